@@ -253,6 +253,10 @@ enum {
     VDBC_RENDER_CACHE_LEAF = 32u,  /* PT, VDB: cache the last leaf only (default, neither
                                       flag: the last leaf and the last lower node).  The
                                       image does not depend on the cache policy. */
+    VDBC_RENDER_INDEX = 128u,      /* VDB: build an index of the leaf regions in the workspace
+                                      first (4 bytes per 8^3 voxels, rebuilt by every call)
+                                      and read the tree through it.  The image does not
+                                      depend on it.  Ignored for dense arrays. */
     VDBC_RENDER_COST_ORDER = 64u   /* PT: hand the tiles to the workgroups in decreasing
                                       order of an estimated cost (the majorant optical
                                       depth of four camera rays per tile) instead of in

@@ -252,6 +252,74 @@ struct VdbAccT {
 
 using VdbAcc = VdbAccT<kCacheLeafLower>;
 
+// Region index of a VDB (built per launch in the caller's workspace): one
+// u32 per 8^3 leaf region, padded by one region on every side so that every
+// corner of a clamped position has an entry.  An entry is where the region's
+// values start, counted from `base` in bytes (WIDE: in floats): a stored leaf
+// at or above `leaf0`, a multiple of its 2 KB, or the one value of a tile or
+// of the background below it.
+struct IndexView {
+    const uint32_t* tab;
+    const uint8_t* base;
+    uint32_t leaf0;
+    int nx, ny, nz;
+    int tx, ty, tz;      // entries per axis
+    float background;
+};
+
+// Accessor over the region index: a corner costs one entry load and one value
+// load wherever it lies, without the tree's descent and without a per-thread
+// cache.  A path tracer's lanes look at unrelated regions, so nearly every
+// lookup of the tree accessor ran the whole descent for some lane of the
+// wave, once per leaf of the footprint.
+template <bool WIDE>
+struct IndexAccT {
+    static constexpr bool kTree = false;
+    IndexView v;
+    __device__ void reset() {}
+    __device__ __forceinline__ float background() const { return v.background; }
+    // Entry at byte offset o of the table.
+    __device__ __forceinline__ uint32_t entry(uint32_t o) const
+    {
+        return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(v.tab) + o);
+    }
+    // Value n (WIDE: of the leaf's floats; else of its bytes) of region e.
+    __device__ __forceinline__ float value(uint32_t e, uint32_t n) const
+    {
+        const uint32_t m = e >= v.leaf0 ? 0xFFFFFFFFu : 0u;
+        const uint32_t o = (n & m) | e;
+        if (WIDE) return reinterpret_cast<const float*>(v.base)[o];
+        return *reinterpret_cast<const float*>(v.base + o);
+    }
+    __device__ __forceinline__ uint32_t table_offset(int i, int j, int k) const
+    {
+        return 4u * ((uint32_t)((i + 8) >> 3) +
+                     (uint32_t)v.tx * ((uint32_t)((j + 8) >> 3) + (uint32_t)v.ty * (uint32_t)((k + 8) >> 3)));
+    }
+    __device__ __forceinline__ void corners(int i, int j, int k, float c[8])
+    {
+        constexpr uint32_t S = WIDE ? 1u : 4u;
+        const bool sx = (i & 7) == 7, sy = (j & 7) == 7, sz = (k & 7) == 7;
+        const uint32_t a0 = S * (uint32_t)((i & 7) + 8 * (j & 7) + 64 * (k & 7));
+        const uint32_t ax = sx ? a0 - 7u * S : a0 + S;
+        const uint32_t ay = sy ? -56u * S : 8u * S, az = sz ? -448u * S : 64u * S;
+        const uint32_t t = table_offset(i, j, k);
+        const uint32_t ox = sx ? 4u : 0u, oy = sy ? 4u * (uint32_t)v.tx : 0u,
+                       oz = sz ? 4u * (uint32_t)v.tx * (uint32_t)v.ty : 0u;
+        const uint32_t e000 = entry(t), e100 = entry(t + ox), e010 = entry(t + oy), e110 = entry(t + oy + ox);
+        const uint32_t e001 = entry(t + oz), e101 = entry(t + oz + ox), e011 = entry(t + oz + oy),
+                       e111 = entry(t + oz + oy + ox);
+        c[0] = value(e000, a0);
+        c[1] = value(e100, ax);
+        c[2] = value(e010, a0 + ay);
+        c[3] = value(e110, ax + ay);
+        c[4] = value(e001, a0 + az);
+        c[5] = value(e101, ax + az);
+        c[6] = value(e011, a0 + ay + az);
+        c[7] = value(e111, ax + ay + az);
+    }
+};
+
 struct DenseView {
     const float* data;
     int nx, ny, nz;

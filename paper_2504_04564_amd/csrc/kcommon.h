@@ -92,6 +92,41 @@ static inline vdbc_status make_view(const vdbc_grid* g, VdbView* v)
     return VDBC_OK;
 }
 
+// Region-index geometry of a volume: entries per axis (a region on every side
+// of the volume) and bytes; 0 bytes where the table would pass 2^32.
+static inline uint64_t index_dims(uint64_t nx, uint64_t ny, uint64_t nz, uint64_t t[3])
+{
+    t[0] = (nx + 7) / 8 + 2;
+    t[1] = (ny + 7) / 8 + 2;
+    t[2] = (nz + 7) / 8 + 2;
+    const double n = (double)t[0] * (double)t[1] * (double)t[2];
+    return n < (double)(1u << 30) ? align256(4ull * t[0] * t[1] * t[2]) : 0;
+}
+
+// The region index of grid g with its table at `tab`; false where the buffer
+// is past what its 32-bit entries reach (4 GB in bytes; wide: 16 GB in floats).
+static inline bool make_index(const vdbc_grid* g, const VdbView& v, uint32_t* tab, IndexView* iv, bool* wide)
+{
+    uint64_t t[3];
+    if (!index_dims((uint64_t)v.nx, (uint64_t)v.ny, (uint64_t)v.nz, t)) return false;
+    Header h;
+    if (parse_header(g->header, g->bytes, &h)) return false;
+    const uint64_t k = (h.off_leaf_values + 2047u) & ~uint64_t(2047u), end = k + 2048ull * h.n_leaf;
+    if (end > (1ull << 34) - 2048) return false;
+    *wide = end > (1ull << 32) - 2048;
+    iv->tab = tab;
+    iv->base = reinterpret_cast<const uint8_t*>(v.leaf_values) - k;
+    iv->leaf0 = (uint32_t)(*wide ? k / 4 : k);
+    iv->nx = v.nx;
+    iv->ny = v.ny;
+    iv->nz = v.nz;
+    iv->tx = (int)t[0];
+    iv->ty = (int)t[1];
+    iv->tz = (int)t[2];
+    iv->background = v.background;
+    return true;
+}
+
 static inline vdbc_status make_dense(const float* dense, vdbc_dims d, float background, DenseView* v)
 {
     if (!dense) return fail(VDBC_E_INVALID, "null dense array");

@@ -3,6 +3,7 @@
 // tracer (Section 4), each for the compressed VDB and for the dense float32
 // baseline through the same templated code, plus batched rendering.
 #include <mutex>
+#include <type_traits>
 
 #include "kcommon.h"
 #include "pt.h"
@@ -130,6 +131,23 @@ __global__ __launch_bounds__(kBlock) void majorant_kernel(View view, MediumK m, 
     Acc acc{view};
     acc.reset();
     majorant_cell(acc, m, C, gx, gy, blockIdx.x, out);
+}
+
+// ---------------------------------------------------------------- region index
+
+// Entries of the region index, one thread each: the region's place in the
+// buffer as the tree resolves it (x fastest, so that the threads of a wave
+// read the same node words).
+__global__ __launch_bounds__(kBlock) void index_kernel(VdbView view, IndexView iv, uint32_t* __restrict__ tab, int shift)
+{
+    const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= (uint32_t)iv.tx * (uint32_t)iv.ty * (uint32_t)iv.tz) return;
+    const uint32_t r = t / (uint32_t)iv.tx;
+    VdbAccT<kCacheNone> acc{view};
+    acc.reset();
+    const LeafH h = acc.resolve((int)(t - r * (uint32_t)iv.tx) - 1, (int)(r % (uint32_t)iv.ty) - 1,
+                                (int)(r / (uint32_t)iv.ty) - 1);
+    tab[t] = (uint32_t)((uint64_t)(reinterpret_cast<const uint8_t*>(h.p) - iv.base) >> shift);
 }
 
 // ---------------------------------------------------------------- EA
@@ -454,6 +472,20 @@ static uint64_t pt_tiles(uint64_t width, uint64_t height, uint64_t tw)
 // order (u32 each).
 static uint64_t pt_order_bytes(uint64_t tiles) { return align256(8ull * kCostBins + 8ull * tiles); }
 
+// Region index of a VDB render (VDBC_RENDER_INDEX): its table follows the
+// rest of the workspace.
+struct IndexPlan {
+    IndexView v{};
+    bool on = false, wide = false;
+};
+
+static vdbc_status launch_index(const VdbView& v, const IndexPlan& ix, hipStream_t st)
+{
+    const uint32_t n = (uint32_t)ix.v.tx * (uint32_t)ix.v.ty * (uint32_t)ix.v.tz;
+    hipLaunchKernelGGL(index_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, v, ix.v,
+                       const_cast<uint32_t*>(ix.v.tab), ix.wide ? 2 : 0);
+    return launch_check("region index");
+}
 
 template <class Acc, class View>
 static vdbc_status launch_majorant(const View& v, const MediumK& m, uint32_t C, float* out,
@@ -467,6 +499,9 @@ static vdbc_status launch_majorant(const View& v, const MediumK& m, uint32_t C, 
                        (int)C, gx, gy, gz, out);
     return launch_check("majorant");
 }
+
+static vdbc_status launch_index_of(const VdbView& v, const IndexPlan& ix, hipStream_t st) { return launch_index(v, ix, st); }
+static vdbc_status launch_index_of(const DenseView&, const IndexPlan&, hipStream_t) { return VDBC_OK; }
 
 // Compute units of the current device (cached per device; 256 if unknown).
 static int device_cus()
@@ -488,7 +523,7 @@ static int device_cus()
 template <class Acc, class View, bool MARCH = true>
 static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_medium* med,
                                const vdbc_render_params* r, float* image, float* aov, void* ws,
-                               uint64_t ws_bytes, void* stream)
+                               uint64_t ws_bytes, void* stream, const IndexPlan& ix = IndexPlan())
 {
     if (!r || !image) return fail(VDBC_E_INVALID, "null params or image");
     CameraK cam;
@@ -644,24 +679,32 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
         if ((s = launch_check("cost order"))) return s;
         order = ord;
     }
+    if (ix.on && (s = launch_index_of(v, ix, st))) return s;
     const size_t lds = 4u * (size_t)g.cwords;
     grid = dim3((unsigned)std::min<uint64_t>(tiles * g.chunks, (uint64_t)device_cus() * kPtBlocksPerCu));
     uint32_t* queue = reinterpret_cast<uint32_t*>(counter + 2);
-#define PT_LAUNCH(CNT, AO, EN)                                                                     \
-    hipLaunchKernelGGL((pt_kernel<Acc, View, CNT, AO, EN>), grid, dim3(kBlock), lds, st, v, cam, m, \
+#define PT_LAUNCH_ACC(ACC, VIEW, FIELD, CNT, AO, EN)                                                  \
+    hipLaunchKernelGGL((pt_kernel<ACC, VIEW, CNT, AO, EN>), grid, dim3(kBlock), lds, st, FIELD, cam, m, \
                        g, maj, coarse, image, aov, counter, queue, sums, order)
-#define PT_LAUNCH_ENV(CNT, AO)           \
-    if (m.env) PT_LAUNCH(CNT, AO, true); \
-    else PT_LAUNCH(CNT, AO, false)
+#define PT_LAUNCH(CNT, AO, EN)                                                          \
+    if constexpr (std::is_same_v<Acc, VdbAcc>) {                                        \
+        if (ix.on && ix.wide) PT_LAUNCH_ACC(IndexAccT<true>, IndexView, ix.v, CNT, AO, EN); \
+        else if (ix.on) PT_LAUNCH_ACC(IndexAccT<false>, IndexView, ix.v, CNT, AO, EN);  \
+        else PT_LAUNCH_ACC(Acc, View, v, CNT, AO, EN);                                  \
+    } else PT_LAUNCH_ACC(Acc, View, v, CNT, AO, EN)
+#define PT_LAUNCH_ENV(CNT, AO)               \
+    if (m.env) { PT_LAUNCH(CNT, AO, true); } \
+    else { PT_LAUNCH(CNT, AO, false); }
     if (count) {
-        if (aov) PT_LAUNCH_ENV(true, true);
-        else PT_LAUNCH_ENV(true, false);
+        if (aov) { PT_LAUNCH_ENV(true, true) }
+        else { PT_LAUNCH_ENV(true, false) }
     } else {
-        if (aov) PT_LAUNCH_ENV(false, true);
-        else PT_LAUNCH_ENV(false, false);
+        if (aov) { PT_LAUNCH_ENV(false, true) }
+        else { PT_LAUNCH_ENV(false, false) }
     }
 #undef PT_LAUNCH_ENV
 #undef PT_LAUNCH
+#undef PT_LAUNCH_ACC
     if (split) {
         if ((s = launch_check("pt render"))) return s;
         hipLaunchKernelGGL(pt_resolve_kernel, dim3((unsigned)((npix + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, sums,
@@ -694,6 +737,10 @@ extern "C" vdbc_status vdbc_render_workspace(const vdbc_render_params* r, vdbc_d
                 return fail(VDBC_E_INVALID, "tile_w must be 0 (default 8), 8, 16, 32 or 64");
             *bytes += pt_order_bytes(pt_tiles(c->width, c->height, r->tile_w == 0 ? 8 : r->tile_w));
         }
+        if (r->flags & VDBC_RENDER_INDEX) {
+            uint64_t t[3];
+            *bytes += index_dims(d.nx, d.ny, d.nz, t);
+        }
     } else {
         *bytes = (r->flags & VDBC_RENDER_COUNT) ? 256 : 0;
     }
@@ -717,7 +764,18 @@ static vdbc_status render_vdb(const vdbc_grid* g, const vdbc_camera* c, const vd
             return render_impl<VdbAccT<kCacheNone>, VdbView, false>(v, c, m, r, image, aov, ws, ws_bytes, stream);
         return render_impl<VdbAccT<kCacheLeaf>, VdbView, false>(v, c, m, r, image, aov, ws, ws_bytes, stream);
     }
-    return render_impl<VdbAcc>(v, c, m, r, image, aov, ws, ws_bytes, stream);
+    IndexPlan ix;
+    if (r && r->mode == VDBC_MODE_PT && (r->flags & VDBC_RENDER_INDEX) && ws) {
+        // the table is the last part of the workspace (its size is checked
+        // with the rest of it below, before anything is enqueued)
+        uint64_t need = 0, t[3];
+        vdbc_dims d{(uint32_t)v.nx, (uint32_t)v.ny, (uint32_t)v.nz};
+        const uint64_t tab = index_dims(d.nx, d.ny, d.nz, t);
+        if ((s = vdbc_render_workspace(r, d, c, &need))) return s;
+        ix.on = tab && make_index(g, v, reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(ws) + need - tab), &ix.v,
+                                  &ix.wide);
+    }
+    return render_impl<VdbAcc>(v, c, m, r, image, aov, ws, ws_bytes, stream, ix);
 }
 
 extern "C" vdbc_status vdbc_render(const vdbc_grid* g, const vdbc_camera* c, const vdbc_medium* m,
