@@ -16,7 +16,7 @@ constexpr uint32_t kMaxBounces = 0xFFFFu;
 // ---------------------------------------------------------------- PT
 
 struct PtArgs {
-    int spp, max_bounces, C, gx, gy, gz, tw;
+    int spp, max_bounces, C, gx, gy, gz, tw, twl;   // tw pixels per wave row, twl = log2 tw
     float invC;
     int lf, cgx, cgy, cgz, cwords;   // coarse blocks of 2^lf macrocells per axis, bit words
     uint32_t seed_lo, seed_hi, frame;
@@ -58,36 +58,91 @@ __global__ __launch_bounds__(kBlock) void coarse_bits_kernel(const float* __rest
     coarse_bits_block(maj, g, bits, blockIdx.x);
 }
 
+// Random words of a lane's path segment (the stream layout of Rng in
+// device.h), generated ahead of their use: a ring of two Philox blocks per
+// lane in LDS, filled at one place of the path loop.  Philox at every draw
+// site ran for a handful of lanes each time (11 % lane utilisation in the free
+// flights, a third of the kernel's VALU instructions).
+struct Stream {
+    uint32_t* ring;    // this lane's word 0; words kBlock apart
+    uint32_t tag;      // stream << 16 | bounce
+    uint32_t d, made;  // words taken, words made
+    __device__ __forceinline__ void start(uint32_t bounce, uint32_t stream)
+    {
+        tag = (stream << 16) | bounce;
+        d = made = 0;
+    }
+    __device__ __forceinline__ void fill(uint32_t k0, uint32_t k1, uint32_t sample, uint32_t frame)
+    {
+        uint32_t w0 = made >> 2, w1 = sample, w2 = tag, w3 = frame;
+        philox4x32_10(w0, w1, w2, w3, k0, k1);
+        uint32_t* r = ring + (made & 4u) * kBlock;
+        r[0] = w0;
+        r[kBlock] = w1;
+        r[2 * kBlock] = w2;
+        r[3 * kBlock] = w3;
+        made += 4u;
+    }
+    __device__ __forceinline__ float next()
+    {
+        const uint32_t x = ring[(d & 7u) * kBlock];
+        ++d;
+        return (float)(x >> 8) * (1.0f / 16777216.0f);
+    }
+};
+
 // One ray segment being tracked through the majorant grid (Section 4): a 3D
 // DDA over macrocells, hierarchical over coarse blocks of macrocells whose
 // occupancy bits live in LDS, and delta tracking inside non-empty cells.
 struct Flight {
-    float o[3], d[3], id[3];
+    float o[3], d[3];
+    // hardware reciprocal of d, +inf for d == +-0
+    float id[3];
+    // what the exit plane of a cell adds to C c along each axis: C - 1/2
+    // (d > 0), -1/2 (d < 0) or +inf (d == 0: no crossing on this axis)
+    float k[3];
     float t, t1, te, mu, imu;
-    int cx, cy, cz, axis;
+    int c[3], axis;
     bool incell, ok;
     uint32_t budget;
 };
 
-// Starts a segment: clip to the box and find the first macrocell.
+// Starts a segment: clip to the box [-0.5, n-0.5]^3 (as box_clip, without
+// branches) and find the first macrocell.
 __device__ __forceinline__ void flight_begin(Flight& f, const PtArgs& g, int nx, int ny, int nz,
                                              const float o[3], const float d[3], float& t0)
 {
+    const float C = (float)g.C;
+    const float hi[3] = {(float)nx - 0.5f, (float)ny - 0.5f, (float)nz - 0.5f};
+    const float last[3] = {(float)(g.gx - 1), (float)(g.gy - 1), (float)(g.gz - 1)};
+    float lo_t = -INFINITY, hi_t = INFINITY;
+    bool ok = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
+        const bool flat = d[a] == 0.0f;
+        const float r = __builtin_amdgcn_rcpf(d[a]);   // hardware reciprocal (<= 1 ulp)
+        const float ta = (-0.5f - o[a]) * r, tb = (hi[a] - o[a]) * r;
+        const float mn = fminf(ta, tb), mx = fmaxf(ta, tb);
+        lo_t = fmaxf(lo_t, flat ? -INFINITY : mn);
+        hi_t = fminf(hi_t, flat ? INFINITY : mx);
+        ok = ok && (!flat || !(o[a] < -0.5f || o[a] > hi[a]));
+        const float k = d[a] > 0.0f ? C - 0.5f : -0.5f;
+        f.k[a] = flat ? INFINITY : k;
+        f.id[a] = flat ? INFINITY : r;
         f.o[a] = o[a];
         f.d[a] = d[a];
-        f.id[a] = __builtin_amdgcn_rcpf(d[a]);   // hardware reciprocal (<= 1 ulp; 1/0 -> inf)
     }
+    t0 = fmaxf(lo_t, 0.0f);
+    f.t1 = hi_t;
+    // a zero or non-finite direction leaves t1 infinite: no segment
+    f.ok = ok && t0 < hi_t && hi_t <= 1.0e30f;
     f.incell = false;
     f.budget = kMaxFlightSamples;
-    f.ok = box_clip(nx, ny, nz, o, d, f.id, t0, f.t1);
     f.t = t0;
-    if (!f.ok) return;
     // the macrocell edge is a power of two: multiplying by its reciprocal is exact
-    f.cx = min(max((int)floorf((fmaf(t0, d[0], o[0]) + 0.5f) * g.invC), 0), g.gx - 1);
-    f.cy = min(max((int)floorf((fmaf(t0, d[1], o[1]) + 0.5f) * g.invC), 0), g.gy - 1);
-    f.cz = min(max((int)floorf((fmaf(t0, d[2], o[2]) + 0.5f) * g.invC), 0), g.gz - 1);
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        f.c[a] = (int)__builtin_amdgcn_fmed3f((fmaf(t0, d[a], o[a]) + 0.5f) * g.invC, 0.0f, last[a]);
 }
 
 __device__ __forceinline__ bool coarse_occupied(const uint32_t* bits, const PtArgs& g, int bx,
@@ -97,125 +152,123 @@ __device__ __forceinline__ bool coarse_occupied(const uint32_t* bits, const PtAr
     return (bits[i >> 5] >> (i & 31u)) & 1u;
 }
 
-// Exit distance through the faces of an axis-aligned cell of edge `edge`
-// (index c along each axis); returns the crossing axis or -1 if t1 is closer.
-__device__ __forceinline__ int cell_exit(const Flight& f, float edge, int cx, int cy, int cz,
+// Exit distance through the faces of the axis-aligned cell of edge `edge` and
+// index c, exit planes at edge c + k; returns the crossing axis or -1 if t1 is
+// closer.  (edge c + k is exact, and a NaN loses every comparison.)
+__device__ __forceinline__ int cell_exit(const Flight& f, float edge, const int c[3], const float k[3],
                                          float& te)
 {
+    float ta[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) ta[a] = (fmaf(edge, (float)c[a], k[a]) - f.o[a]) * f.id[a];
     te = f.t1;
     int axis = -1;
-    if (f.d[0] != 0.0f) {
-        const float ta = (edge * (float)(cx + (f.d[0] > 0.0f)) - 0.5f - f.o[0]) * f.id[0];
-        if (ta < te) {
-            te = ta;
-            axis = 0;
-        }
-    }
-    if (f.d[1] != 0.0f) {
-        const float ta = (edge * (float)(cy + (f.d[1] > 0.0f)) - 0.5f - f.o[1]) * f.id[1];
-        if (ta < te) {
-            te = ta;
-            axis = 1;
-        }
-    }
-    if (f.d[2] != 0.0f) {
-        const float ta = (edge * (float)(cz + (f.d[2] > 0.0f)) - 0.5f - f.o[2]) * f.id[2];
-        if (ta < te) {
-            te = ta;
-            axis = 2;
-        }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const bool nearer = ta[a] < te;
+        te = nearer ? ta[a] : te;
+        axis = nearer ? a : axis;
     }
     return axis;
+}
+
+// -log(x) for x in [2^-24, 1], bit for bit __logf's: its scaling of denormals
+// and its infinities left out.
+__device__ __forceinline__ float neg_log(float x)
+{
+    const float y = __builtin_amdgcn_logf(x), c = __uint_as_float(0x3F317217u), cc = __uint_as_float(0x3377D1CFu);
+    const float e = fmaf(y, cc, fmaf(y, c, -(y * c)));
+    return -fmaf(y, c, e);
 }
 
 // Advances the flight to its next tentative collision: returns 1 with f.t
 // at the collision (the caller samples the density there and makes the
 // accept test), 0 when the segment leaves the grid without one, or
-// kFlightYield after entering kWalkCells macrocells without a collision (call
-// again to continue; the walk and its random draws are the same as without
-// the pause).  Empty cells draw no random
+// kFlightYield after entering `walk` <= kWalkCells macrocells without a
+// collision (call again to continue; the walk and its random draws are the
+// same as without the pause).  Takes at most walk + 1 draws from `rng`, walk
+// when the flight is not inside a cell yet.  Empty cells draw no random
 // numbers and coarse-block faces are macrocell faces, so the tentative
 // collisions are those of a uniform walk over every macrocell; a flight that
 // overshoots a cell restarts at its exit (memorylessness).
+//
+// Every lane of the wave takes the same kWalkCells + 1 turns (draw and step,
+// then look the next cell up) under a flag instead of leaving the loop where
+// its own walk ends: the flight's state then stays in place, where exits out
+// of the middle cost some fifty register moves a turn.
 __device__ __forceinline__ int flight_advance(Flight& f, const float* __restrict__ maj, const uint32_t* cbits,
-                                              const PtArgs& g, Rng& rng, uint32_t& ncell)
+                                              const PtArgs& g, Stream& rng, int walk, uint32_t& ncell)
 {
-    if (!f.ok) return 0;
     const float C = (float)g.C;
-    const float CF = (float)(g.C << g.lf);
-    int walk = kWalkCells;
-    for (;;) {
-        if (f.incell) {
-            f.t = fmaf(-__logf(1.0f - rng.next()), f.imu, f.t);
-            if (f.t < f.te) {
-                if (--f.budget == 0) return 0;
-                return 1;
+    const int F = 1 << g.lf;
+    int result = f.ok ? kFlightYield : 0;
+    bool run = f.ok;
+#pragma unroll 1
+    for (int turn = 0;; ++turn) {
+        bool step = false;
+        if (run && f.incell) {
+            f.t = fmaf(neg_log(1.0f - rng.next()), f.imu, f.t);
+            f.incell = f.t < f.te;
+            step = !f.incell;
+            if (f.incell) {
+                run = false;
+                result = --f.budget == 0 ? 0 : 1;
             }
-            f.incell = false;
-            if (f.axis < 0) return 0;
+        }
+        if (step) {
             f.t = f.te;
-            if (f.axis == 0) {
-                f.cx += f.d[0] > 0.0f ? 1 : -1;
-                if ((unsigned)f.cx >= (unsigned)g.gx) return 0;
-            } else if (f.axis == 1) {
-                f.cy += f.d[1] > 0.0f ? 1 : -1;
-                if ((unsigned)f.cy >= (unsigned)g.gy) return 0;
-            } else {
-                f.cz += f.d[2] > 0.0f ? 1 : -1;
-                if ((unsigned)f.cz >= (unsigned)g.gz) return 0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) f.c[a] += f.axis != a ? 0 : f.k[a] > 0.0f ? 1 : -1;
+            if (f.axis < 0 || (unsigned)f.c[0] >= (unsigned)g.gx || (unsigned)f.c[1] >= (unsigned)g.gy ||
+                (unsigned)f.c[2] >= (unsigned)g.gz) {
+                run = false;
+                result = 0;
             }
         }
-        if (--walk < 0) return kFlightYield;
-        const int bx = f.cx >> g.lf, by = f.cy >> g.lf, bz = f.cz >> g.lf;
-        ++ncell;
-        if (!coarse_occupied(cbits, g, bx, by, bz)) {
-            // cross the empty block in one step
-            float te;
-            const int axis = cell_exit(f, CF, bx, by, bz, te);
-            if (axis < 0) return 0;
-            f.t = te;
-            const int F = 1 << g.lf;
-            const float px = (fmaf(te, f.d[0], f.o[0]) + 0.5f) * g.invC;
-            const float py = (fmaf(te, f.d[1], f.o[1]) + 0.5f) * g.invC;
-            const float pz = (fmaf(te, f.d[2], f.o[2]) + 0.5f) * g.invC;
-            if (axis == 0) {
-                f.cx = f.d[0] > 0.0f ? (bx + 1) * F : bx * F - 1;
-                if ((unsigned)f.cx >= (unsigned)g.gx) return 0;
+        run = run && turn < walk;
+        if (turn == kWalkCells) return result;
+        if (run) {
+            ++ncell;
+            const int b[3] = {f.c[0] >> g.lf, f.c[1] >> g.lf, f.c[2] >> g.lf};
+            if (!coarse_occupied(cbits, g, b[0], b[1], b[2])) {
+                // cross the empty block in one step
+                const float CF = C * (float)F;
+                float kf[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) kf[a] = f.k[a] > 0.0f ? f.k[a] + (CF - C) : f.k[a];
+                const int axis = cell_exit(f, CF, b, kf, f.t);
+                const int n[3] = {g.gx, g.gy, g.gz};
+                bool out = axis < 0;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float p = (fmaf(f.t, f.d[a], f.o[a]) + 0.5f) * g.invC;
+                    const int lo = b[a] * F, hi = lo + F;
+                    const int in = min(max((int)floorf(p), lo), min(hi, n[a]) - 1);
+                    const int to = f.k[a] > 0.0f ? hi : lo - 1;
+                    f.c[a] = axis == a ? to : in;
+                    out = out || (unsigned)f.c[a] >= (unsigned)n[a];
+                }
+                if (out) {
+                    run = false;
+                    result = 0;
+                }
             } else {
-                f.cx = min(max((int)floorf(px), bx * F), min(bx * F + F, g.gx) - 1);
+                f.axis = cell_exit(f, C, f.c, f.k, f.te);
+                f.mu = maj[f.c[0] + g.gx * (f.c[1] + g.gy * f.c[2])];
+                f.incell = f.mu > 0.0f && f.t < f.te;
+                f.imu = __builtin_amdgcn_rcpf(f.mu);   // hardware reciprocal (<= 1 ulp)
+                if (!f.incell) {
+                    // an empty cell inside an occupied block
+                    f.t = f.te;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) f.c[a] += f.axis != a ? 0 : f.k[a] > 0.0f ? 1 : -1;
+                    if (f.axis < 0 || (unsigned)f.c[0] >= (unsigned)g.gx || (unsigned)f.c[1] >= (unsigned)g.gy ||
+                        (unsigned)f.c[2] >= (unsigned)g.gz) {
+                        run = false;
+                        result = 0;
+                    }
+                }
             }
-            if (axis == 1) {
-                f.cy = f.d[1] > 0.0f ? (by + 1) * F : by * F - 1;
-                if ((unsigned)f.cy >= (unsigned)g.gy) return 0;
-            } else {
-                f.cy = min(max((int)floorf(py), by * F), min(by * F + F, g.gy) - 1);
-            }
-            if (axis == 2) {
-                f.cz = f.d[2] > 0.0f ? (bz + 1) * F : bz * F - 1;
-                if ((unsigned)f.cz >= (unsigned)g.gz) return 0;
-            } else {
-                f.cz = min(max((int)floorf(pz), bz * F), min(bz * F + F, g.gz) - 1);
-            }
-            continue;
-        }
-        f.axis = cell_exit(f, C, f.cx, f.cy, f.cz, f.te);
-        f.mu = maj[f.cx + g.gx * (f.cy + g.gy * f.cz)];
-        if (f.mu > 0.0f && f.t < f.te) {
-            f.incell = true;
-            f.imu = __builtin_amdgcn_rcpf(f.mu);   // hardware reciprocal (<= 1 ulp)
-            continue;
-        }
-        if (f.axis < 0) return 0;
-        f.t = f.te;
-        if (f.axis == 0) {
-            f.cx += f.d[0] > 0.0f ? 1 : -1;
-            if ((unsigned)f.cx >= (unsigned)g.gx) return 0;
-        } else if (f.axis == 1) {
-            f.cy += f.d[1] > 0.0f ? 1 : -1;
-            if ((unsigned)f.cy >= (unsigned)g.gy) return 0;
-        } else {
-            f.cz += f.d[2] > 0.0f ? 1 : -1;
-            if ((unsigned)f.cz >= (unsigned)g.gz) return 0;
         }
     }
 }
@@ -235,6 +288,7 @@ struct TileShared {
     long long rgb[kBlock][3];
     long long depth[kBlock];
     unsigned int hits[kBlock], escapes[kBlock];
+    uint32_t ring[8 * kBlock];   // random words ahead, two Philox blocks per lane
     unsigned int next;
 };
 
@@ -264,11 +318,11 @@ __device__ __forceinline__ void pt_tile(Acc& acc, int nx, int ny, int nz, const 
                                         uint32_t& nseg, uint32_t s0, uint32_t s1, PtSums sums)
 {
     const int tid = threadIdx.x;
-    const int tw = g.tw, th = 64 / g.tw;
-    // the four waves sit side by side in one band of th rows: wave w covers
-    // columns [x0 + w tw, x0 + (w + 1) tw), so the tile is 4 tw x th pixels
+    // the four waves sit side by side in one band of 64 / tw rows: wave w covers
+    // columns [x0 + w tw, x0 + (w + 1) tw), so the tile is 4 tw x 64 / tw pixels
     // (256 x 1 at tw = 64: neighbouring waves trace neighbouring rays)
-    const int x0 = bx * 4 * tw, y0 = by * th;
+    const int tl = g.twl;   // log2 tw
+    const int x0 = bx << (tl + 2), y0 = by << (6 - tl);
     ts.rgb[tid][0] = ts.rgb[tid][1] = ts.rgb[tid][2] = 0;
     ts.depth[tid] = 0;
     ts.hits[tid] = ts.escapes[tid] = 0;
@@ -277,127 +331,139 @@ __device__ __forceinline__ void pt_tile(Acc& acc, int nx, int ny, int nz, const 
     const uint32_t total = kBlock * s1;
     const float inv4pi = 0.0795774715459476679f;
     uint32_t u = s0 * kBlock + (uint32_t)tid;
-    int q = 0, px = 0, py = 0;
-    uint32_t k0 = 0, smp = 0;
+    uint32_t k0 = 0;
     float L0 = 0.0f, L1 = 0.0f, L2 = 0.0f, b0 = 1.0f, b1 = 1.0f, b2 = 1.0f;
     float t0p = 0.0f, pdepth = 1.0f;
     bool phit = false;
     int b = 0;
-    bool shadow = false, fresh = true;
-    Rng rng;
+    enum { kFlying, kCamera, kShadow, kScatter };
+    int begin = kCamera;      // the segment to begin, kFlying inside one
+    bool shadow = false;
+    Stream rng;
+    rng.ring = ts.ring + tid;
     Flight f;
     while (u < total) {
-        if (fresh) {
-            q = (int)(u & (kBlock - 1));
-            smp = u >> 8;
-            const int w = q >> 6, l = q & 63;
-            px = x0 + w * tw + (l % tw);
-            py = y0 + (l / tw);
-            if (px >= cam.width || py >= cam.height) {   // no pixel here
-                u = atomicAdd(&ts.next, 1u);
-                continue;
-            }
-            fresh = false;
+        bool dead = false;   // the path ends here without a flight
+        if (begin == kCamera) {
+            const int q = (int)(u & (kBlock - 1)), l = q & 63;
+            const int px = x0 + ((q >> 6) << tl) + (l & ((1 << tl) - 1)), py = y0 + (l >> tl);
+            dead = px >= cam.width || py >= cam.height;   // no pixel here
             k0 = g.seed_lo ^ ((uint32_t)py * (uint32_t)cam.width + (uint32_t)px);
-            rng.init(k0, g.seed_hi, smp, 0u, 0u, g.frame);
-            const float jx = rng.next(), jy = rng.next();
-            float o[3], d[3];
-            camera_ray(cam, (float)px + jx, (float)py + jy, o, d);
+            rng.start(0u, 0u);
             b = 0;
-            shadow = false;
             L0 = L1 = L2 = 0.0f;
             b0 = b1 = b2 = 1.0f;
-            flight_begin(f, g, nx, ny, nz, o, d, t0p);
-            ++nseg;   // camera ray
         }
-        const int tentative = flight_advance(f, maj, cbits, g, rng, ncell);
-        if (tentative == kFlightYield) continue;
-        // the density at the tentative collision is taken here, after the walk
-        // loop, so that the lanes of a wave that reached one in different
-        // steps of the walk sample in one pass
-        float sv = 0.0f;
-        if (tentative) {
-            sv = trilinear(acc, fmaf(f.t, f.d[0], f.o[0]), fmaf(f.t, f.d[1], f.o[1]), fmaf(f.t, f.d[2], f.o[2]));
-            ++nsamp;
-        }
-        const bool hit = tentative && rng.next() * f.mu < m.ds * tf_alpha_at(tf_lds, m, sv);
-        if (tentative && !hit) continue;    // null collision: keep tracking
-        bool path_done = false, next_bounce = false;
-        if (!shadow) {
-            if (b == 0) {
-                phit = hit;
-                pdepth = hit ? (f.t - t0p) / (f.t1 - t0p) : 1.0f;
-            }
-            if (hit) {
-                // real collision: weight by albedo and colour, then the
-                // shadow ray towards the light from the collision point
-                const float4 c = tf_eval(m, sv);
-                b0 *= m.albedo * c.x;
-                b1 *= m.albedo * c.y;
-                b2 *= m.albedo * c.z;
-                const float x[3] = {fmaf(f.t, f.d[0], f.o[0]), fmaf(f.t, f.d[1], f.o[1]),
-                                    fmaf(f.t, f.d[2], f.o[2])};
-                rng.init(k0, g.seed_hi, smp, (uint32_t)b, 1u, g.frame);
-                float t0s;
-                flight_begin(f, g, nx, ny, nz, x, m.light, t0s);
-                ++nseg;   // shadow ray
-                shadow = true;
+        // random words of this turn: at most four are taken below
+        if (rng.made - rng.d < 4u) rng.fill(k0, g.seed_hi, u >> 8, g.frame);
+        if (begin != kFlying) {
+            float o[3] = {f.o[0], f.o[1], f.o[2]}, d[3];
+            if (begin == kCamera) {
+                const int q = (int)(u & (kBlock - 1)), l = q & 63;
+                const int px = x0 + ((q >> 6) << tl) + (l & ((1 << tl) - 1)), py = y0 + (l >> tl);
+                const float jx = rng.next(), jy = rng.next();
+                camera_ray(cam, (float)px + jx, (float)py + jy, o, d);
+            } else if (begin == kShadow) {
+                d[0] = m.light[0];
+                d[1] = m.light[1];
+                d[2] = m.light[2];
             } else {
-                float e0, e1, e2;
-                if (ENV) {   // the map's lookup only where a map is bound
-                    escape_radiance(m, f.d, e0, e1, e2);
-                } else {
-                    e0 = m.ambient[0];
-                    e1 = m.ambient[1];
-                    e2 = m.ambient[2];
+                // segment b: isotropic scattering from the collision point
+                // (the shadow ray's origin) with the first two draws of its
+                // stream; with Russian roulette one survival draw comes first
+                // (from bounce 2 on: survive with q = min(1, max throughput),
+                // survivors carry throughput / q)
+                if (g.rr) {
+                    const float ur = rng.next();
+                    const float qs = b >= 2 ? fminf(fmaxf(fmaxf(b0, b1), b2), 1.0f) : 1.0f;
+                    if (ur < qs) {
+                        b0 /= qs;
+                        b1 /= qs;
+                        b2 /= qs;
+                    } else {
+                        dead = true;
+                    }
                 }
-                L0 = fmaf(b0, e0, L0);
-                L1 = fmaf(b1, e1, L1);
-                L2 = fmaf(b2, e2, L2);
-                path_done = true;
+                const float u1 = rng.next(), u2 = rng.next();
+                const float z = 1.0f - 2.0f * u1;
+                const float r = sqrtf(fmaxf(0.0f, 1.0f - z * z));
+                const float phi = 6.28318530717958647692f * u2;
+                d[0] = r * __cosf(phi);
+                d[1] = r * __sinf(phi);
+                d[2] = z;
             }
-        } else {
-            if (!hit) {
-                L0 = fmaf(b0 * inv4pi, m.light_E[0], L0);
-                L1 = fmaf(b1 * inv4pi, m.light_E[1], L1);
-                L2 = fmaf(b2 * inv4pi, m.light_E[2], L2);
-            }
-            shadow = false;
-            if (b + 1 == g.max_bounces) path_done = true;
-            else next_bounce = true;
+            float t0;
+            flight_begin(f, g, nx, ny, nz, o, d, t0);
+            if (AOV && begin == kCamera) t0p = t0;
+            if (!dead) ++nseg;
+            begin = kFlying;
         }
-        if (next_bounce) {
-            // segment b + 1: isotropic scattering from the collision point
-            // (the shadow ray's origin) with the first two draws of its
-            // stream; with Russian roulette one survival draw comes first
-            // (from bounce 2 on: survive with q = min(1, max throughput),
-            // survivors carry throughput / q)
-            ++b;
-            rng.init(k0, g.seed_hi, smp, (uint32_t)b, 0u, g.frame);
-            if (g.rr) {
-                const float ur = rng.next();
-                const float qs = b >= 2 ? fminf(fmaxf(fmaxf(b0, b1), b2), 1.0f) : 1.0f;
-                if (ur < qs) {
-                    b0 /= qs;
-                    b1 /= qs;
-                    b2 /= qs;
+        bool path_done = dead;
+        if (!dead) {
+            // a turn takes at most walk + 1 draws in flight (walk outside a
+            // cell) and one for the accept test
+            const int left = (int)(rng.made - rng.d) - (f.incell ? 2 : 1);
+            const int tentative = flight_advance(f, maj, cbits, g, rng, min(kWalkCells, left), ncell);
+            if (tentative == kFlightYield) continue;
+            // the density at the tentative collision is taken here, after the walk
+            // loop, so that the lanes of a wave that reached one in different
+            // steps of the walk sample in one pass
+            float sv = 0.0f;
+            if (tentative) {
+                sv = trilinear(acc, fmaf(f.t, f.d[0], f.o[0]), fmaf(f.t, f.d[1], f.o[1]), fmaf(f.t, f.d[2], f.o[2]));
+                ++nsamp;
+            }
+            const bool hit = tentative && rng.next() * f.mu < m.ds * tf_alpha_at(tf_lds, m, sv);
+            if (tentative && !hit) continue;    // null collision: keep tracking
+            if (!shadow) {
+                if (b == 0) {
+                    phit = hit;
+                    if (AOV) pdepth = hit ? (f.t - t0p) / (f.t1 - t0p) : 1.0f;
+                }
+                if (hit) {
+                    // real collision: weight by albedo and colour, then the
+                    // shadow ray towards the light from the collision point
+                    const float4 c = tf_eval(m, sv);
+                    b0 *= m.albedo * c.x;
+                    b1 *= m.albedo * c.y;
+                    b2 *= m.albedo * c.z;
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) f.o[a] = fmaf(f.t, f.d[a], f.o[a]);
+                    rng.start((uint32_t)b, 1u);
+                    begin = kShadow;
+                    shadow = true;
                 } else {
+                    float e0, e1, e2;
+                    if (ENV) {   // the map's lookup only where a map is bound
+                        escape_radiance(m, f.d, e0, e1, e2);
+                    } else {
+                        e0 = m.ambient[0];
+                        e1 = m.ambient[1];
+                        e2 = m.ambient[2];
+                    }
+                    L0 = fmaf(b0, e0, L0);
+                    L1 = fmaf(b1, e1, L1);
+                    L2 = fmaf(b2, e2, L2);
                     path_done = true;
                 }
+            } else {
+                if (!hit) {
+                    L0 = fmaf(b0 * inv4pi, m.light_E[0], L0);
+                    L1 = fmaf(b1 * inv4pi, m.light_E[1], L1);
+                    L2 = fmaf(b2 * inv4pi, m.light_E[2], L2);
+                }
+                shadow = false;
+                if (b + 1 == g.max_bounces) {
+                    path_done = true;
+                } else {
+                    ++b;
+                    rng.start((uint32_t)b, 0u);
+                    begin = kScatter;
+                }
             }
         }
-        if (next_bounce && !path_done) {
-            const float u1 = rng.next(), u2 = rng.next();
-            const float z = 1.0f - 2.0f * u1;
-            const float r = sqrtf(fmaxf(0.0f, 1.0f - z * z));
-            const float phi = 6.28318530717958647692f * u2;
-            const float o[3] = {f.o[0], f.o[1], f.o[2]};
-            const float d[3] = {r * __cosf(phi), r * __sinf(phi), z};
-            float t0n;
-            flight_begin(f, g, nx, ny, nz, o, d, t0n);
-            ++nseg;   // scattered ray
-        }
         if (path_done) {
+            const int q = (int)(u & (kBlock - 1));
             atomicAdd(reinterpret_cast<unsigned long long*>(&ts.rgb[q][0]), (unsigned long long)to_fixed(L0));
             atomicAdd(reinterpret_cast<unsigned long long*>(&ts.rgb[q][1]), (unsigned long long)to_fixed(L1));
             atomicAdd(reinterpret_cast<unsigned long long*>(&ts.rgb[q][2]), (unsigned long long)to_fixed(L2));
@@ -405,13 +471,13 @@ __device__ __forceinline__ void pt_tile(Acc& acc, int nx, int ny, int nz, const 
                                (unsigned long long)to_fixed(pdepth));
             atomicAdd(phit ? &ts.hits[q] : &ts.escapes[q], 1u);
             u = atomicAdd(&ts.next, 1u);
-            fresh = true;
+            begin = kCamera;
         }
     }
     __syncthreads();
     {
         const int w = tid >> 6, l = tid & 63;
-        const int qx = x0 + w * tw + (l % tw), qy = y0 + (l / tw);
+        const int qx = x0 + (w << tl) + (l & ((1 << tl) - 1)), qy = y0 + (l >> tl);
         if (qx < cam.width && qy < cam.height) {
             const uint32_t pix = (uint32_t)qy * (uint32_t)cam.width + (uint32_t)qx;
             if (sums.rgbn) {

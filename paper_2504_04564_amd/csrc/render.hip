@@ -635,6 +635,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     g.spp = (int)r->spp;
     g.max_bounces = (int)r->max_bounces;
     g.tw = r->tile_w == 0 ? 8 : (int)r->tile_w;
+    g.twl = __builtin_ctz((unsigned)g.tw);
     g.seed_lo = (uint32_t)r->seed;
     g.seed_hi = (uint32_t)(r->seed >> 32);
     g.frame = r->frame;
@@ -1011,6 +1012,7 @@ static vdbc_status batch_plan(const vdbc_batch_item* items, uint32_t n, const vd
         g.spp = (int)it.spp;
         g.max_bounces = (int)it.max_bounces;
         g.tw = (int)t.tile_w;
+        g.twl = __builtin_ctz((unsigned)g.tw);
         g.seed_lo = (uint32_t)it.seed;
         g.seed_hi = (uint32_t)(it.seed >> 32);
         g.frame = it.frame;

@@ -1,0 +1,101 @@
+"""Rendering through the region index (VDBC_RENDER_INDEX): the index only says
+where each 8^3 region's values start, so images, AOVs and counters are those of
+the tree accessor bit for bit.  Volumes at the edges of the table: ragged
+sizes, one voxel, nothing stored, tiles at both levels, values negative and
+large, and a buffer past 4 GB (entries in floats instead of bytes)."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_2504_04564_amd import _build, vdbc
+from synth import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    _build.ensure_built()
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return vdbc.load()
+
+
+def _bits(t):
+    return t.view(torch.int32).cpu().numpy()
+
+
+def _plain(r):
+    """The renderer's launch without the index, in the same workspace."""
+    flags = r.prm.flags
+    assert flags & vdbc.RENDER_INDEX
+    r.prm.flags = flags & ~vdbc.RENDER_INDEX
+    r.ws.fill_(0xA5)
+    r.image.fill_(-1.0)
+    img = _bits(r.launch()).copy()
+    r.prm.flags = flags
+    return img
+
+
+def _volume(name):
+    rng = np.random.default_rng(7)
+    if name == "ragged":
+        return synth.cloud_volume((37, 50, 71), seed=3), 0.25, {}
+    if name == "edge8":   # sizes of 8k - 1, 8k, 8k + 1
+        return rng.random((15, 16, 17), dtype=np.float32), 1.0, {}
+    if name == "one":
+        return np.full((1, 1, 1), 0.7, np.float32), 1.0, {}
+    if name == "empty":   # no leaf at all
+        return np.zeros((40, 33, 20), np.float32), 0.5, dict(flags=vdbc.NO_CORNERS)
+    if name == "tiles":   # an upper tile, lower tiles and leaves
+        v = np.zeros((160, 160, 160), np.float32)
+        v[:128, :128, :128] = 0.25
+        v[128:152, 8:24, 64:96] = 0.5
+        v[130, 10:20, 66] = 1.0
+        return v, 1.0, {}
+    return synth.mid_volume(n=96), 0.10, dict(partial=(0.5, 1e30))
+
+
+@pytest.mark.parametrize("name", ["ragged", "edge8", "one", "empty", "tiles", "partial"])
+@pytest.mark.parametrize("chunk,flags", [(0, 0), (2, vdbc.RENDER_COST_ORDER | vdbc.RENDER_RR)])
+def test_path_traced_images_with_and_without_the_index(name, chunk, flags):
+    v, rate, kw = _volume(name)
+    g = vdbc.Grid(vdbc.encode(v, rate, **kw)[0])
+    cam = scenes.orbit_camera(g.dims, 45, 35)
+    for med in (scenes.pt_medium(16.0), scenes.pt_medium_tf5(64.0)):
+        prm = dict(spp=5, max_bounces=6, macrocell=8, seed=11, chunk_spp=chunk, flags=flags | vdbc.RENDER_COUNT)
+        r = vdbc.Renderer(g, cam, med, prm, vdbc.MODE_PT, aov=True)
+        want = _plain(r)
+        aov, counts = _bits(r.aov).copy(), (r.sample_count(), r.segment_count(), r.cell_count())
+        r.ws.fill_(0xA5)
+        assert np.array_equal(_bits(r.launch()), want)
+        assert np.array_equal(_bits(r.aov), aov)
+        assert (r.sample_count(), r.segment_count(), r.cell_count()) == counts
+
+
+def test_index_workspace_and_cache_policy():
+    g = vdbc.Grid(vdbc.encode(synth.tiny_volume(), 0.25)[0])
+    cam, med = scenes.orbit_camera(g.dims, 16, 16), scenes.pt_medium(16.0)
+    a = vdbc.Renderer(g, cam, med, dict(spp=2, macrocell=8), vdbc.MODE_PT)
+    # 64^3: 8 regions and two of the border on each axis
+    b = vdbc.Renderer(g, cam, med, dict(spp=2, macrocell=8, flags=vdbc.RENDER_CACHE_LEAF), vdbc.MODE_PT)
+    assert a.ws_bytes - b.ws_bytes == (4 * 10 ** 3 + 255) // 256 * 256
+    assert not b.prm.flags & vdbc.RENDER_INDEX
+    assert np.array_equal(_bits(a.launch()), _bits(b.launch()))
+
+
+def test_buffer_past_4_gb_takes_wide_entries():
+    n = 1056   # 4.7 GB of values, all stored
+    x = np.arange(n, dtype=np.float32)
+    v = np.empty((n, n, n), np.float32)
+    for z in range(n):
+        v[z] = ((x[:, None] * 3.0 + x[None, :] * 7.0 + z * 5.0) % 61.0) / 61.0
+    buf, _ = vdbc.encode(v, 1.0, flags=vdbc.BG_EXPLICIT)
+    assert buf.size > 1 << 32
+    g = vdbc.Grid(buf)
+    del v, buf
+    cam = scenes.orbit_camera(g.dims, 64, 48)
+    r = vdbc.Renderer(g, cam, scenes.pt_medium(16.0), dict(spp=2, max_bounces=4, macrocell=64, seed=5), vdbc.MODE_PT)
+    want = _plain(r)
+    assert np.array_equal(_bits(r.launch()), want)
+    assert float(r.image[..., 3].max()) > 0.0
