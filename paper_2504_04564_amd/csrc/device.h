@@ -271,6 +271,10 @@ struct IndexView {
     uint32_t leaf0;
     int nx, ny, nz;
     int tx, ty, tz;      // entries per axis
+    // marchers: per entry the log2 of the largest aligned block of entries
+    // (1, 2, 4 or 8 a side) all of whose voxel footprints read the background
+    // alone, plus one; 0 where a footprint reaches a stored leaf or a tile
+    const uint8_t* level;
     float background;
 };
 
@@ -442,17 +446,18 @@ __device__ __forceinline__ void escape_radiance(const MediumK& m, const float d[
     b = p[2];
 }
 
-__device__ __forceinline__ float4 tf_eval(const MediumK& m, float s)
+__device__ __forceinline__ float4 tf_eval_at(const float4* tf, const MediumK& m, float s)
 {
     float pos = (s - m.tf_lo) * m.tf_inv;
     pos = fminf(fmaxf(pos, 0.0f), (float)(m.tf_n - 1));
     int i = (int)pos;
     i = i > m.tf_n - 2 ? m.tf_n - 2 : i;
     const float fr = pos - (float)i;
-    const float4 a = m.tf[i], b = m.tf[i + 1];
+    const float4 a = tf[i], b = tf[i + 1];
     return make_float4(lerp(a.x, b.x, fr), lerp(a.y, b.y, fr), lerp(a.z, b.z, fr),
                        lerp(a.w, b.w, fr));
 }
+__device__ __forceinline__ float4 tf_eval(const MediumK& m, float s) { return tf_eval_at(m.tf, m, s); }
 
 // tf_alpha with the control points read from `tf` (an LDS copy of m.tf).
 __device__ __forceinline__ float tf_alpha_at(const float4* tf, const MediumK& m, float s)

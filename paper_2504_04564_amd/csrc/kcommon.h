@@ -123,6 +123,7 @@ static inline bool make_index(const vdbc_grid* g, const VdbView& v, uint32_t* ta
     iv->tx = (int)t[0];
     iv->ty = (int)t[1];
     iv->tz = (int)t[2];
+    iv->level = nullptr;
     iv->background = v.background;
     return true;
 }

@@ -2,6 +2,7 @@
 // emission-absorption and iso-surface marching, and the delta-tracking path
 // tracer (Section 4), each for the compressed VDB and for the dense float32
 // baseline through the same templated code, plus batched rendering.
+#include <climits>
 #include <mutex>
 #include <type_traits>
 
@@ -148,6 +149,296 @@ __global__ __launch_bounds__(kBlock) void index_kernel(VdbView view, IndexView i
     const LeafH h = acc.resolve((int)(t - r * (uint32_t)iv.tx) - 1, (int)(r % (uint32_t)iv.ty) - 1,
                                 (int)(r / (uint32_t)iv.ty) - 1);
     tab[t] = (uint32_t)((uint64_t)(reinterpret_cast<const uint8_t*>(h.p) - iv.base) >> shift);
+}
+
+// The same entries with their skip levels (see IndexView::level): a workgroup
+// takes 8^3 entries, resolves them and their upper neighbours (9^3), and one
+// wave reduces the emptiness of the footprints over 2^3, 4^3 and 8^3 blocks, a
+// row of eight entries a lane.  Larger blocks would leave the chip idle (16^3:
+// 125 workgroups at 512^3).
+__global__ __launch_bounds__(kBlock) void index_level_kernel(VdbView view, IndexView iv, uint32_t* __restrict__ tab,
+                                                             uint8_t* __restrict__ level, int shift)
+{
+    __shared__ uint32_t row[9][9];   // [z][y]: bit x set where a stored leaf or a tile is
+    const uint32_t nbx = (uint32_t)(iv.tx + 7) / 8u, nby = (uint32_t)(iv.ty + 7) / 8u, bq = blockIdx.x / nbx;
+    const int x0 = (int)(blockIdx.x - bq * nbx) * 8, y0 = (int)(bq % nby) * 8, z0 = (int)(bq / nby) * 8, t = threadIdx.x;
+    if (t < 81) (&row[0][0])[t] = 0u;
+    __syncthreads();
+    VdbAccT<kCacheNone> acc{view};
+    acc.reset();
+    auto resolve = [&](int i, int j, int k, bool own) {
+        const int x = x0 + i, y = y0 + j, z = z0 + k;
+        const LeafH h = acc.resolve(x - 1, y - 1, z - 1);
+        if (h.p != view.bg) atomicOr(&row[k][j], 1u << i);
+        if (own && x < iv.tx && y < iv.ty && z < iv.tz)
+            tab[(uint32_t)x + (uint32_t)iv.tx * ((uint32_t)y + (uint32_t)iv.ty * (uint32_t)z)] =
+                (uint32_t)((uint64_t)(reinterpret_cast<const uint8_t*>(h.p) - iv.base) >> shift);
+    };
+    const int u = t & 7, v = (t >> 3) & 7, w = t >> 6;
+    resolve(u, v, w, true);
+    resolve(u, v, w + 4, true);
+    // the faces x = 8, y = 8 and z = 8 (64 each), their edges (8 each), the corner
+    if (w < 3) resolve(w == 0 ? 8 : u, w == 1 ? 8 : w == 0 ? u : v, w == 2 ? 8 : v, false);
+    else if (v < 3) resolve(v == 0 ? u : 8, v == 1 ? u : 8, v == 2 ? u : 8, false);
+    else if (t == 192 + 24) resolve(8, 8, 8, false);
+    __syncthreads();
+    if (t >= 64) return;
+    // lane t: the row of entries y0 + v, z0 + t / 8, bit x
+    const int j = u, k = t >> 3;
+    const uint32_t m = row[k][j] | row[k][j + 1] | row[k + 1][j] | row[k + 1][j + 1];
+    auto block = [&](uint32_t e, int s, uint32_t keep) {   // e over blocks of 2 s entries a side
+        e &= __shfl_xor(e, s);
+        e &= __shfl_xor(e, 8 * s);
+        e &= (e >> s) & keep;
+        return e;
+    };
+    const uint32_t e1 = ~(m | (m >> 1)) & 0xFFu;
+    const uint32_t e2 = block(e1, 1, 0x55u) * 0x3u, e3 = block(e2, 2, 0x11u) * 0xFu, e4 = block(e3, 4, 0x01u) * 0xFFu;
+    const int y = y0 + j, z = z0 + k;
+    if (y >= iv.ty || z >= iv.tz) return;
+    uint8_t* out = level + x0 + (size_t)iv.tx * ((size_t)y + (size_t)iv.ty * (size_t)z);
+    for (int i = 0; i < 8 && x0 + i < iv.tx; ++i)
+        out[i] = (uint8_t)(((e1 >> i) & 1u) + ((e2 >> i) & 1u) + ((e3 >> i) & 1u) + ((e4 >> i) & 1u));
+}
+
+// ---------------------------------------------------------------- marching in quads
+// The EA and ISO marchers of a dense array, and of a VDB read through the
+// region index: four lanes (a quad) share a ray and take four consecutive
+// lattice samples at a time, sixteen rays (4 x 4 pixels) a wave.  One thread
+// per ray left the chip waiting (a sample's loads, then the next one's) and
+// its waves half empty, since 64 rays end at 64 different places.  Per sample
+// the arithmetic, and the order of the sums, are those of the kernels below
+// with one thread per ray; the images are the same bit for bit.
+
+// Lane S of the quad's value of v, in every lane of the quad.
+template <int S>
+__device__ __forceinline__ float quad_get(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), S * 0x55, 0xF, 0xF, true));
+}
+template <int S>
+__device__ __forceinline__ int quad_get(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, S * 0x55, 0xF, 0xF, true);
+}
+
+// A quad's ray: the lattice t0 + (k + 1/2) step inside the volume's box.
+struct MarchRay {
+    float o[3], d[3], id[3], t0, t1;
+    int px, py;
+    bool live;
+};
+
+template <class View>
+__device__ __forceinline__ MarchRay march_ray(const View& v, const CameraK& cam)
+{
+    MarchRay r;
+    const int q = (threadIdx.x & 63) >> 2, w = threadIdx.x >> 6;
+    const uint32_t across = (uint32_t)(cam.width + 7) / 8u, by = blockIdx.x / across, bx = blockIdx.x - by * across;
+    r.px = (int)bx * 8 + (w & 1) * 4 + (q & 3);
+    r.py = (int)by * 8 + (w >> 1) * 4 + (q >> 2);
+    r.live = r.px < cam.width && r.py < cam.height;
+    camera_ray(cam, (float)r.px + 0.5f, (float)r.py + 0.5f, r.o, r.d);
+    for (int a = 0; a < 3; ++a) r.id[a] = 1.0f / r.d[a];
+    if (!box_clip(v.nx, v.ny, v.nz, r.o, r.d, r.id, r.t0, r.t1)) r.live = false;
+    return r;
+}
+
+// The first lattice index past the empty block of level L (2^(L - 1) entries
+// a side) that holds sample k in entry e; at least k + 1.  Every sample
+// before it reads the background (kHddaEps: far beyond the rounding of the
+// exit and of a sample's position).
+__device__ __forceinline__ int march_skip(const MarchRay& r, int L, const int e[3], int k, float inv_step)
+{
+    const int keep = -(1 << (L - 1)), size = 8 << (L - 1);
+    float te = INFINITY;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float lo = (float)(8 * ((e[a] & keep) - 1));
+        const float plane = r.d[a] > 0.0f ? lo + ((float)size - kHddaEps) : lo + kHddaEps;
+        te = r.d[a] == 0.0f ? te : fminf(te, (plane - r.o[a]) * r.id[a]);
+    }
+    const int kn = (int)floorf(fminf(fmaf(te - r.t0, inv_step, -0.5f), 2.0e9f));
+    return max(kn, k) + 1;
+}
+
+// Ray parameter and position of lattice sample k, with SKIP its index entry
+// and that entry's skip level (0 without); false past the end of the ray.
+template <bool SKIP, class View>
+__device__ __forceinline__ bool march_at(const View& v, const MarchRay& r, int k, float step, float& t, float p[3],
+                                         int e[3], int& L)
+{
+    t = fmaf((float)k + 0.5f, step, r.t0);
+    const int n[3] = {v.nx, v.ny, v.nz};
+    const bool in = t < r.t1;
+    L = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) p[a] = fmaf(t, r.d[a], r.o[a]);
+    if constexpr (SKIP) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            e[a] = ((int)floorf(__builtin_amdgcn_fmed3f(p[a], -2.0f, (float)n[a] + 1.0f)) + 8) >> 3;
+        if (in) L = v.level[(uint32_t)e[0] + (uint32_t)v.tx * ((uint32_t)e[1] + (uint32_t)v.ty * (uint32_t)e[2])];
+    }
+    return in;
+}
+
+// Emission-absorption.  SKIP: the transfer function is clear at the
+// background, so that samples in empty blocks add nothing.
+template <class Acc, class View, bool SKIP>
+__global__ __launch_bounds__(kBlock) void ea_quad_kernel(View view, CameraK cam, MediumK m, float step,
+                                                         float inv_step, float t_term, float* __restrict__ image)
+{
+    __shared__ float4 tf[64];
+    for (int i = threadIdx.x; i < m.tf_n; i += kBlock) tf[i] = m.tf[i];
+    __syncthreads();
+    Acc acc{view};
+    acc.reset();
+    const MarchRay r = march_ray(view, cam);
+    float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, T = 1.0f;
+    const int lane = threadIdx.x & 3;
+    bool run = r.live;
+    int k = 0;
+    while (run) {
+        // the next four samples that are not all empty
+        float t, p[3];
+        int e[3], L;
+        bool in;
+        for (;;) {
+            in = march_at<SKIP>(view, r, k + lane, step, t, p, e, L);
+            const int sample = in && L == 0;
+            if (quad_get<0>(sample) | quad_get<1>(sample) | quad_get<2>(sample) | quad_get<3>(sample)) break;
+            // the quad's samples are all empty or past the end
+            const int next = SKIP && in ? march_skip(r, L, e, k + lane, inv_step) : INT_MAX;
+            k = quad_get<3>(next);
+            if (k == INT_MAX) break;
+        }
+        if (k == INT_MAX) break;
+        float4 c = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float alpha = 0.0f;
+        if (in && L == 0) {
+            const float s = trilinear(acc, p[0], p[1], p[2]);
+            c = tf_eval_at(tf, m, s);
+            alpha = 1.0f - expf(-(m.ds * c.w) * step);
+        }
+#define VDBC_EA_ADD(S)                                                  \
+    {                                                                   \
+        const float a = run ? quad_get<S>(alpha) : 0.0f, ta = T * a;    \
+        c0 = fmaf(ta, quad_get<S>(c.x), c0);                            \
+        c1 = fmaf(ta, quad_get<S>(c.y), c1);                            \
+        c2 = fmaf(ta, quad_get<S>(c.z), c2);                            \
+        T *= 1.0f - a;                                                  \
+        run = run && !(T < t_term);                                     \
+    }
+        VDBC_EA_ADD(0)
+        VDBC_EA_ADD(1)
+        VDBC_EA_ADD(2)
+        VDBC_EA_ADD(3)
+#undef VDBC_EA_ADD
+        k += 4;
+    }
+    if (lane == 0 && r.px < cam.width && r.py < cam.height)
+        reinterpret_cast<float4*>(image)[(uint64_t)r.py * cam.width + r.px] = make_float4(c0, c1, c2, 1.0f - T);
+}
+
+// Iso-surface (see iso_kernel).  With SKIP the samples of empty blocks take
+// the background's side without a field read.
+template <class Acc, class View, bool SKIP>
+__global__ __launch_bounds__(kBlock) void iso_quad_kernel(View view, CameraK cam, float iso, float step, float inv_step,
+                                                          int refine, float* __restrict__ image,
+                                                          float* __restrict__ aov)
+{
+    Acc acc{view};
+    acc.reset();
+    const MarchRay r = march_ray(view, cam);
+    const int lane = threadIdx.x & 3;
+    const bool bg_side = acc.background() >= iso;
+    bool run = r.live, have = false, prev = false, cross = false;
+    float lo = 0.0f, hi = 0.0f;
+    int k = 0;
+    while (run) {
+        float t, p[3];
+        int e[3], L;
+        bool in;
+        for (;;) {
+            in = march_at<SKIP>(view, r, k + lane, step, t, p, e, L);
+            const int sample = in && L == 0;
+            if (quad_get<0>(sample) | quad_get<1>(sample) | quad_get<2>(sample) | quad_get<3>(sample)) break;
+            // all empty or past the end; an empty sample after one on the
+            // other side is a crossing
+            const bool first = quad_get<0>((int)in);
+            if (!first) k = INT_MAX;
+            if (!first || (have && prev != bg_side)) break;
+            have = true;
+            prev = bg_side;
+            const int next = SKIP && in ? march_skip(r, L, e, k + lane, inv_step) : INT_MAX;
+            k = quad_get<3>(next);
+            if (k == INT_MAX) break;
+        }
+        if (k == INT_MAX) break;
+        bool side = bg_side;
+        if (in && L == 0) side = trilinear(acc, p[0], p[1], p[2]) >= iso;
+        const int mine = (in ? 1 : 0) | (side ? 2 : 0);
+        // the first sample on another side than the one before it
+#define VDBC_ISO_STEP(S)                                                                  \
+    {                                                                                     \
+        const int b = quad_get<S>(mine);                                                  \
+        const bool at = run && (b & 1) && have && ((b & 2) != 0) != prev;                 \
+        if (at) {                                                                         \
+            lo = fmaf((float)(k + S - 1) + 0.5f, step, r.t0);                             \
+            hi = fmaf((float)(k + S) + 0.5f, step, r.t0);                                 \
+            cross = true;                                                                 \
+            run = false;                                                                  \
+        }                                                                                 \
+        if (run && (b & 1)) {                                                             \
+            have = true;                                                                  \
+            prev = (b & 2) != 0;                                                          \
+        }                                                                                 \
+    }
+        VDBC_ISO_STEP(0)
+        VDBC_ISO_STEP(1)
+        VDBC_ISO_STEP(2)
+        VDBC_ISO_STEP(3)
+#undef VDBC_ISO_STEP
+        k += 4;
+    }
+    float4 out = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float thit = -1.0f;
+    if (cross) {
+        // two bisection steps a turn: lane 0 takes the midpoint, lanes 1 and 2
+        // the midpoints of the halves it can leave
+        for (int it = 0; it < refine; it += 2) {
+            const float mid = 0.5f * (lo + hi), below = 0.5f * (lo + mid), above = 0.5f * (mid + hi);
+            const float q = lane == 1 ? below : lane == 2 ? above : mid;
+            const int same =
+                (trilinear(acc, fmaf(q, r.d[0], r.o[0]), fmaf(q, r.d[1], r.o[1]), fmaf(q, r.d[2], r.o[2])) >= iso) ==
+                prev;
+            const bool up = quad_get<0>(same);
+            if (up) lo = mid;
+            else hi = mid;
+            if (it + 1 == refine) break;
+            const bool up2 = up ? quad_get<2>(same) : quad_get<1>(same);
+            const float mid2 = up ? above : below;
+            if (up2) lo = mid2;
+            else hi = mid2;
+        }
+        // the six central-difference samples of the normal in two turns
+        thit = 0.5f * (lo + hi);
+        const float sh = (lane & 1) ? -0.5f : 0.5f;
+        const float p0 = fmaf(thit, r.d[0], r.o[0]), p1 = fmaf(thit, r.d[1], r.o[1]), p2 = fmaf(thit, r.d[2], r.o[2]);
+        const float wxy = trilinear(acc, p0 + (lane < 2 ? sh : 0.0f), p1 + (lane < 2 ? 0.0f : sh), p2);
+        const float wz = trilinear(acc, p0, p1, p2 + sh);
+        const float gx = quad_get<0>(wxy) - quad_get<1>(wxy), gy = quad_get<2>(wxy) - quad_get<3>(wxy),
+                    gz = quad_get<0>(wz) - quad_get<1>(wz);
+        const float len = sqrtf(gx * gx + gy * gy + gz * gz);
+        out = len > 0.0f ? make_float4(0.5f * (1.0f - gx / len), 0.5f * (1.0f - gy / len), 0.5f * (1.0f - gz / len), 1.0f)
+                         : make_float4(0.5f, 0.5f, 0.5f, 1.0f);
+    }
+    if (lane == 0 && r.px < cam.width && r.py < cam.height) {
+        const uint64_t pix = (uint64_t)r.py * cam.width + r.px;
+        reinterpret_cast<float4*>(image)[pix] = out;
+        if (aov) reinterpret_cast<float2*>(aov)[pix] = make_float2(thit, 0.0f);
+    }
 }
 
 // ---------------------------------------------------------------- EA
@@ -481,6 +772,12 @@ struct IndexPlan {
 
 static vdbc_status launch_index(const VdbView& v, const IndexPlan& ix, hipStream_t st)
 {
+    if (ix.v.level) {
+        const unsigned blocks = (unsigned)((ix.v.tx + 7) / 8) * (unsigned)((ix.v.ty + 7) / 8) * (unsigned)((ix.v.tz + 7) / 8);
+        hipLaunchKernelGGL(index_level_kernel, dim3(blocks), dim3(kBlock), 0, st, v, ix.v, const_cast<uint32_t*>(ix.v.tab),
+                           const_cast<uint8_t*>(ix.v.level), ix.wide ? 2 : 0);
+        return launch_check("region index");
+    }
     const uint32_t n = (uint32_t)ix.v.tx * (uint32_t)ix.v.ty * (uint32_t)ix.v.tz;
     hipLaunchKernelGGL(index_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, v, ix.v,
                        const_cast<uint32_t*>(ix.v.tab), ix.wide ? 2 : 0);
@@ -518,6 +815,19 @@ static int device_cus()
     return cus;
 }
 
+// Whether the marchers may skip empty blocks where the caller did not ask for
+// it: the image stays the same bit for bit while a sample's position is
+// rounded by far less than kHddaEps, i.e. while the camera is near.
+static bool skip_is_exact(const CameraK& c, const VdbView& v)
+{
+    double far = (double)v.nx + v.ny + v.nz;
+    for (int a = 0; a < 3; ++a)
+        far += c.kind == 1 ? std::fabs((double)c.o[a])
+                           : std::fabs((double)c.ll[a]) + std::fabs((double)c.du[a]) * c.width +
+                                 std::fabs((double)c.dv[a]) * c.height;
+    return far <= 16384.0;
+}
+
 // MARCH = false leaves out the EA and ISO kernels (accessor variants that
 // only the path tracer uses).
 template <class Acc, class View, bool MARCH = true>
@@ -547,6 +857,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     if (ws && reinterpret_cast<uintptr_t>(ws) % 256)
         return fail(VDBC_E_INVALID, "workspace must be 256-byte aligned");
     dim3 grid((cam.width + kTile - 1) / kTile, (cam.height + kTile - 1) / kTile);
+    const dim3 quads((unsigned)((cam.width + 7) / 8) * (unsigned)((cam.height + 7) / 8));
     if constexpr (MARCH) {
         if (r->mode == VDBC_MODE_ISO) {
             if (!(r->step > 0.0f) || !std::isfinite(r->step))
@@ -561,6 +872,27 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
                 if ((s = launch_check("zero counter"))) return s;
             }
             const bool hdda = (r->flags & VDBC_RENDER_HDDA) != 0;
+#define ISO_QUAD(ACC, VIEW, FIELD, SKIP)                                                                          \
+    hipLaunchKernelGGL((iso_quad_kernel<ACC, VIEW, SKIP>), quads, dim3(kBlock), 0, st, FIELD, cam, r->iso, r->step, \
+                       1.0f / r->step, (int)r->refine, image, aov)
+            if constexpr (std::is_same_v<Acc, DenseAcc>) {
+                if (count)
+                    hipLaunchKernelGGL((iso_kernel<Acc, View, false, true>), grid, dim3(kBlock), 0, st, v, cam, r->iso,
+                                       r->step, (int)r->refine, image, aov, counter);
+                else
+                    ISO_QUAD(DenseAcc, DenseView, v, false);
+                return launch_check("iso render");
+            } else {
+            if (ix.on && !count) {
+                if ((s = launch_index(v, ix, st))) return s;
+                const bool skip = hdda || skip_is_exact(cam, v);
+                if (ix.wide && skip) ISO_QUAD(IndexAccT<true>, IndexView, ix.v, true);
+                else if (ix.wide) ISO_QUAD(IndexAccT<true>, IndexView, ix.v, false);
+                else if (skip) ISO_QUAD(IndexAccT<false>, IndexView, ix.v, true);
+                else ISO_QUAD(IndexAccT<false>, IndexView, ix.v, false);
+                return launch_check("iso render");
+            }
+#undef ISO_QUAD
     #define ISO_LAUNCH(H, CNT)                                                                      \
         hipLaunchKernelGGL((iso_kernel<Acc, View, H, CNT>), grid, dim3(kBlock), 0, st, v, cam, r->iso, \
                            r->step, (int)r->refine, image, aov, counter)
@@ -573,6 +905,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
             }
     #undef ISO_LAUNCH
             return launch_check("iso render");
+            }
         }
         if (count && r->mode == VDBC_MODE_EA) {
             hipLaunchKernelGGL(zero_u64, dim3(1), dim3(64), 0, st, counter);
@@ -585,7 +918,29 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
             const double diag = std::sqrt((double)v.nx * v.nx + (double)v.ny * v.ny + (double)v.nz * v.nz);
             if (diag / r->step > 16777216.0)
                 return fail(VDBC_E_INVALID, "EA step too small for this volume (> 2^24 samples per ray)");
-            const bool hdda = (r->flags & VDBC_RENDER_HDDA) && host_alpha(m, v.background) == 0.0f;
+            const bool clear = host_alpha(m, v.background) == 0.0f;
+            const bool hdda = (r->flags & VDBC_RENDER_HDDA) && clear;
+#define EA_QUAD(ACC, VIEW, FIELD, SKIP)                                                                          \
+    hipLaunchKernelGGL((ea_quad_kernel<ACC, VIEW, SKIP>), quads, dim3(kBlock), 0, st, FIELD, cam, m, r->step, \
+                       1.0f / r->step, r->t_terminate, image)
+            if constexpr (std::is_same_v<Acc, DenseAcc>) {
+                if (count)
+                    hipLaunchKernelGGL((ea_kernel<Acc, View, false, true>), grid, dim3(kBlock), 0, st, v, cam, m,
+                                       r->step, r->t_terminate, image, counter);
+                else
+                    EA_QUAD(DenseAcc, DenseView, v, false);
+                return launch_check("ea render");
+            } else {
+            if (ix.on && !count) {
+                if ((s = launch_index(v, ix, st))) return s;
+                const bool skip = clear && (hdda || skip_is_exact(cam, v));
+                if (ix.wide && skip) EA_QUAD(IndexAccT<true>, IndexView, ix.v, true);
+                else if (ix.wide) EA_QUAD(IndexAccT<true>, IndexView, ix.v, false);
+                else if (skip) EA_QUAD(IndexAccT<false>, IndexView, ix.v, true);
+                else EA_QUAD(IndexAccT<false>, IndexView, ix.v, false);
+                return launch_check("ea render");
+            }
+#undef EA_QUAD
     #define EA_LAUNCH(H, CNT)                                                                      \
         hipLaunchKernelGGL((ea_kernel<Acc, View, H, CNT>), grid, dim3(kBlock), 0, st, v, cam, m, \
                            r->step, r->t_terminate, image, counter)
@@ -598,6 +953,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
             }
     #undef EA_LAUNCH
             return launch_check("ea render");
+            }
         }
     } else if (r->mode != VDBC_MODE_PT) {
         return fail(VDBC_E_UNSUPPORTED, "accessor variant for the path tracer only");
@@ -744,6 +1100,10 @@ extern "C" vdbc_status vdbc_render_workspace(const vdbc_render_params* r, vdbc_d
         }
     } else {
         *bytes = (r->flags & VDBC_RENDER_COUNT) ? 256 : 0;
+        if (r->flags & VDBC_RENDER_INDEX) {
+            uint64_t t[3];
+            if (index_dims(d.nx, d.ny, d.nz, t)) *bytes += index_dims(d.nx, d.ny, d.nz, t) + align256(t[0] * t[1] * t[2]);
+        }
     }
     return VDBC_OK;
 }
@@ -766,15 +1126,17 @@ static vdbc_status render_vdb(const vdbc_grid* g, const vdbc_camera* c, const vd
         return render_impl<VdbAccT<kCacheLeaf>, VdbView, false>(v, c, m, r, image, aov, ws, ws_bytes, stream);
     }
     IndexPlan ix;
-    if (r && r->mode == VDBC_MODE_PT && (r->flags & VDBC_RENDER_INDEX) && ws) {
+    if (r && r->mode <= 2 && (r->flags & VDBC_RENDER_INDEX) && ws) {
         // the table is the last part of the workspace (its size is checked
         // with the rest of it below, before anything is enqueued)
         uint64_t need = 0, t[3];
         vdbc_dims d{(uint32_t)v.nx, (uint32_t)v.ny, (uint32_t)v.nz};
         const uint64_t tab = index_dims(d.nx, d.ny, d.nz, t);
         if ((s = vdbc_render_workspace(r, d, c, &need))) return s;
-        ix.on = tab && make_index(g, v, reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(ws) + need - tab), &ix.v,
-                                  &ix.wide);
+        const uint64_t levels = tab && r->mode != VDBC_MODE_PT ? align256(t[0] * t[1] * t[2]) : 0;
+        uint8_t* const at = static_cast<uint8_t*>(ws) + need - tab - levels;
+        ix.on = tab && make_index(g, v, reinterpret_cast<uint32_t*>(at), &ix.v, &ix.wide);
+        if (levels) ix.v.level = at + tab;
     }
     return render_impl<VdbAcc>(v, c, m, r, image, aov, ws, ws_bytes, stream, ix);
 }

@@ -389,7 +389,7 @@ class Renderer:
         self.prm = params_c(params, mode)
         # the tree is read through a region index in the workspace, unless an
         # accessor cache policy is asked for
-        if not self.dense and mode == MODE_PT and not self.prm.flags & (RENDER_CACHE_NONE | RENDER_CACHE_LEAF):
+        if not self.dense and not self.prm.flags & (RENDER_CACHE_NONE | RENDER_CACHE_LEAF):
             self.prm.flags |= RENDER_INDEX
         ws = C.c_uint64(0)
         _check(load().vdbc_render_workspace(C.byref(self.prm), self.dims, C.byref(self.cam), C.byref(ws)))
