@@ -104,7 +104,8 @@ static inline uint64_t index_dims(uint64_t nx, uint64_t ny, uint64_t nz, uint64_
 }
 
 // The region index of grid g with its table at `tab`; false where the buffer
-// is past what its 32-bit entries reach (4 GB in bytes; wide: 16 GB in floats).
+// is past what its 32-bit entries reach (16 GB, in floats).  *wide: past 4 GB,
+// what they reach in bytes (set on entry: floats whatever the size).
 static inline bool make_index(const vdbc_grid* g, const VdbView& v, uint32_t* tab, IndexView* iv, bool* wide)
 {
     uint64_t t[3];
@@ -113,7 +114,7 @@ static inline bool make_index(const vdbc_grid* g, const VdbView& v, uint32_t* ta
     if (parse_header(g->header, g->bytes, &h)) return false;
     const uint64_t k = (h.off_leaf_values + 2047u) & ~uint64_t(2047u), end = k + 2048ull * h.n_leaf;
     if (end > (1ull << 34) - 2048) return false;
-    *wide = end > (1ull << 32) - 2048;
+    *wide = *wide || end > (1ull << 32) - 2048;
     iv->tab = tab;
     iv->base = reinterpret_cast<const uint8_t*>(v.leaf_values) - k;
     iv->leaf0 = (uint32_t)(*wide ? k / 4 : k);

@@ -2,12 +2,18 @@
 // DDA with coarse-block skipping, the per-tile path pool, the persistent
 // single-volume kernel and the batched multi-volume kernel.
 #pragma once
+#include <type_traits>
+
 #include "kcommon.h"
 
 namespace vdbc {
 
-// Resident PT workgroups per compute unit (the kernel's launch bounds).
-constexpr int kPtBlocksPerCu = 4;
+// Resident PT workgroups per compute unit (the kernel's launch bounds): the
+// tree accessor needs the registers of four, the others fit five (512^3 frame
+// 6.40 ms with four, 6.07 with five).
+template <class Acc>
+constexpr int kPtBlocksPerCu = std::is_same_v<Acc, IndexAccT<false>> || std::is_same_v<Acc, IndexAccT<true>> ||
+                                       std::is_same_v<Acc, DenseAcc> ? 5 : 4;
 // Largest samples per pixel (256 x spp work units per tile fit 32 bits) and
 // bounces per path (the bounce is a 16-bit field of the Philox counter).
 constexpr uint32_t kMaxSpp = 1u << 16;
@@ -591,7 +597,7 @@ __global__ void pt_cost_scatter_kernel(const uint32_t* __restrict__ key, uint32_
 }
 
 template <class Acc, class View, bool COUNT, bool AOV, bool ENV>
-__global__ __launch_bounds__(kBlock, 4) void pt_kernel(View view, CameraK cam, MediumK m, PtArgs g,
+__global__ __launch_bounds__(kBlock, kPtBlocksPerCu<Acc>) void pt_kernel(View view, CameraK cam, MediumK m, PtArgs g,
                                                     const float* __restrict__ maj,
                                                     const uint32_t* __restrict__ coarse,
                                                     float* __restrict__ image,
@@ -645,6 +651,7 @@ __global__ __launch_bounds__(kBlock, 4) void pt_kernel(View view, CameraK cam, M
 // (item = tile * g.chunks + chunk), which add into the volume's pixel sums.
 struct BatchDesc {
     VdbView view;
+    IndexView index;   // when the batch reads its volumes through their region indexes
     CameraK cam;
     MediumK med;
     PtArgs g;
@@ -660,7 +667,8 @@ __global__ void zero_u32(uint32_t* p)
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0u;
 }
 
-__global__ __launch_bounds__(kBlock, 4) void pt_batch_kernel(const BatchDesc* __restrict__ descs,
+template <class Acc, bool ENV>
+__global__ __launch_bounds__(kBlock, kPtBlocksPerCu<Acc>) void pt_batch_kernel(const BatchDesc* __restrict__ descs,
                                                           const uint32_t* __restrict__ items,
                                                           uint32_t n_items, uint32_t* counter)
 {
@@ -683,13 +691,14 @@ __global__ __launch_bounds__(kBlock, 4) void pt_batch_kernel(const BatchDesc* __
         for (int i = threadIdx.x; i < g.cwords; i += kBlock) cbits[i] = D->coarse[i];
         for (int i = threadIdx.x; i < D->med.tf_n; i += kBlock) tf_lds[i] = D->med.tf[i];
         __syncthreads();
-        VdbAcc acc{D->view};
+        Acc acc;
+        if constexpr (std::is_same_v<Acc, VdbAcc>) acc.v = D->view;
+        else acc.v = D->index;
         acc.reset();
         uint32_t ns = 0, nc = 0, nsg = 0;
-        pt_tile<VdbAcc, false, true>(acc, D->view.nx, D->view.ny, D->view.nz, cam, D->med, g, D->maj, cbits,
-                               (int)(tile % (uint32_t)D->tiles_x), (int)(tile / (uint32_t)D->tiles_x), ts,
-                               tf_lds, D->image, nullptr, ns, nc, nsg, s0, min(s0 + g.chunk, (uint32_t)g.spp),
-                               D->sums);
+        pt_tile<Acc, false, ENV>(acc, D->view.nx, D->view.ny, D->view.nz, cam, D->med, g, D->maj, cbits,
+                                 (int)(tile % (uint32_t)D->tiles_x), (int)(tile / (uint32_t)D->tiles_x), ts, tf_lds,
+                                 D->image, nullptr, ns, nc, nsg, s0, min(s0 + g.chunk, (uint32_t)g.spp), D->sums);
     }
 }
 

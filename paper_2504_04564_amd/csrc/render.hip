@@ -136,12 +136,11 @@ __global__ __launch_bounds__(kBlock) void majorant_kernel(View view, MediumK m, 
 
 // ---------------------------------------------------------------- region index
 
-// Entries of the region index, one thread each: the region's place in the
-// buffer as the tree resolves it (x fastest, so that the threads of a wave
-// read the same node words).
-__global__ __launch_bounds__(kBlock) void index_kernel(VdbView view, IndexView iv, uint32_t* __restrict__ tab, int shift)
+// Entry t of the region index: the region's place in the buffer as the tree
+// resolves it.
+__device__ __forceinline__ void index_entry(const VdbView& view, const IndexView& iv, uint32_t t,
+                                            uint32_t* __restrict__ tab, int shift)
 {
-    const uint32_t t = blockIdx.x * kBlock + threadIdx.x;
     if (t >= (uint32_t)iv.tx * (uint32_t)iv.ty * (uint32_t)iv.tz) return;
     const uint32_t r = t / (uint32_t)iv.tx;
     VdbAccT<kCacheNone> acc{view};
@@ -149,6 +148,13 @@ __global__ __launch_bounds__(kBlock) void index_kernel(VdbView view, IndexView i
     const LeafH h = acc.resolve((int)(t - r * (uint32_t)iv.tx) - 1, (int)(r % (uint32_t)iv.ty) - 1,
                                 (int)(r / (uint32_t)iv.ty) - 1);
     tab[t] = (uint32_t)((uint64_t)(reinterpret_cast<const uint8_t*>(h.p) - iv.base) >> shift);
+}
+
+// One thread per entry (x fastest, so that the threads of a wave read the
+// same node words).
+__global__ __launch_bounds__(kBlock) void index_kernel(VdbView view, IndexView iv, uint32_t* __restrict__ tab, int shift)
+{
+    index_entry(view, iv, blockIdx.x * kBlock + threadIdx.x, tab, shift);
 }
 
 // The same entries with their skip levels (see IndexView::level): a workgroup
@@ -1038,7 +1044,8 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     }
     if (ix.on && (s = launch_index_of(v, ix, st))) return s;
     const size_t lds = 4u * (size_t)g.cwords;
-    grid = dim3((unsigned)std::min<uint64_t>(tiles * g.chunks, (uint64_t)device_cus() * kPtBlocksPerCu));
+    const int per_cu = ix.on ? kPtBlocksPerCu<IndexAccT<false>> : kPtBlocksPerCu<Acc>;
+    grid = dim3((unsigned)std::min<uint64_t>(tiles * g.chunks, (uint64_t)device_cus() * (uint64_t)per_cu));
     uint32_t* queue = reinterpret_cast<uint32_t*>(counter + 2);
 #define PT_LAUNCH_ACC(ACC, VIEW, FIELD, CNT, AO, EN)                                                  \
     hipLaunchKernelGGL((pt_kernel<ACC, VIEW, CNT, AO, EN>), grid, dim3(kBlock), lds, st, FIELD, cam, m, \
@@ -1281,6 +1288,15 @@ __global__ __launch_bounds__(kBlock) void majorant_batch_kernel(const BatchDesc*
     majorant_cell(acc, D->med, D->g.C, D->g.gx, D->g.gy, blockIdx.x - base[v], const_cast<float*>(D->maj));
 }
 
+__global__ __launch_bounds__(kBlock) void index_batch_kernel(const BatchDesc* __restrict__ descs,
+                                                             const uint32_t* __restrict__ base, uint32_t n, int shift)
+{
+    const uint32_t v = batch_volume_of(base, n, blockIdx.x);
+    const BatchDesc* D = descs + v;
+    index_entry(D->view, D->index, (blockIdx.x - base[v]) * kBlock + threadIdx.x, const_cast<uint32_t*>(D->index.tab),
+                shift);
+}
+
 __global__ __launch_bounds__(kBlock) void coarse_bits_batch_kernel(const BatchDesc* __restrict__ descs,
                                                                    const uint32_t* __restrict__ base, uint32_t n)
 {
@@ -1312,7 +1328,12 @@ struct vdbc_batch {
     uint32_t* d_counter = nullptr;
     uint32_t* d_cell_base = nullptr;     // prefix tables of macrocells and coarse-bit workgroups
     uint32_t* d_coarse_base = nullptr;
-    uint64_t cells_total = 0, cblocks_total = 0;
+    uint32_t* d_index_base = nullptr;    // ... and of index workgroups
+    uint64_t cells_total = 0, cblocks_total = 0, iblocks_total = 0;
+    // region indexes of all volumes (in bytes, or wide where one of them
+    // needs it), or of none where one cannot have any
+    std::vector<IndexPlan> index;
+    bool indexed = false, wide = false, env = false;
     uint32_t n_items = 0;
     int max_cwords = 0;
     int grid_blocks = 0;
@@ -1347,7 +1368,8 @@ static uint64_t batch_sums_bytes(uint64_t npix) { return align256(32ull * npix);
 // a volume that is not split) and the total size.
 static vdbc_status batch_plan(const vdbc_batch_item* items, uint32_t n, const vdbc_tuning& t, vdbc_batch* b,
                               std::vector<uint64_t>* maj_off, std::vector<uint64_t>* coarse_off,
-                              std::vector<uint64_t>* sums_off, uint64_t* items_off, uint64_t* total)
+                              std::vector<uint64_t>* sums_off, std::vector<uint64_t>* index_off,
+                              uint64_t* items_off, uint64_t* total)
 {
     if (!items || n == 0 || n > 4096) return fail(VDBC_E_INVALID, "need 1..4096 batch items");
     b->n = n;
@@ -1399,7 +1421,7 @@ static vdbc_status batch_plan(const vdbc_batch_item* items, uint32_t n, const vd
     uint64_t o = 256;                                   // counter
     const uint64_t descs_off = o;
     o += align256((uint64_t)n * sizeof(BatchDesc));
-    o += align256(8ull * (n + 1));                      // the two prefix tables of the batched majorants
+    o += align256(12ull * (n + 1));                     // the prefix tables of the batched set-up launches
     *items_off = o;
     o += align256(tiles_total * 4);
     for (uint32_t i = 0; i < n; ++i) {
@@ -1413,6 +1435,9 @@ static vdbc_status batch_plan(const vdbc_batch_item* items, uint32_t n, const vd
         } else {
             sums_off->push_back(0);
         }
+        uint64_t e[3];
+        index_off->push_back(o);
+        o += index_dims((uint64_t)b->views[i].nx, (uint64_t)b->views[i].ny, (uint64_t)b->views[i].nz, e);
     }
     (void)descs_off;
     b->n_items = (uint32_t)tiles_total;
@@ -1440,7 +1465,8 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
     // the persistent launch builds every volume's majorant grid and coarse
     // bits in one launch each (below the grid-size limit); one launch per
     // volume otherwise, and for the per-volume baseline
-    const bool batched_pre = b->t.persistent && b->cells_total < (1ull << 24) && b->cblocks_total < (1ull << 24);
+    const bool batched_pre = b->t.persistent && b->cells_total < (1ull << 24) && b->cblocks_total < (1ull << 24) &&
+                             b->iblocks_total < (1ull << 24);
     if (batched_pre) {
         hipLaunchKernelGGL(majorant_batch_kernel, dim3((unsigned)b->cells_total), dim3(kBlock), 0, st, b->d_descs,
                            b->d_cell_base, b->n);
@@ -1448,6 +1474,11 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
         hipLaunchKernelGGL(coarse_bits_batch_kernel, dim3((unsigned)b->cblocks_total), dim3(kBlock), 0, st,
                            b->d_descs, b->d_coarse_base, b->n);
         if ((s = launch_check("batched coarse occupancy"))) return s;
+        if (b->indexed) {
+            hipLaunchKernelGGL(index_batch_kernel, dim3((unsigned)b->iblocks_total), dim3(kBlock), 0, st, b->d_descs,
+                               b->d_index_base, b->n, b->wide ? 2 : 0);
+            if ((s = launch_check("batched region indexes"))) return s;
+        }
     }
     for (uint32_t i = 0; i < b->n; ++i) {
         if (!batched_pre) {
@@ -1458,6 +1489,7 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
             hipLaunchKernelGGL(coarse_bits_kernel, dim3((unsigned)((ncoarse + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                                st, b->majs[i], g, b->coarse[i]);
             if ((s = launch_check("batch coarse occupancy"))) return s;
+            if (b->indexed && (s = launch_index(b->views[i], b->index[i], st))) return s;
         }
         if (b->sums[i].rgbn) {
             const uint64_t words = batch_sums_bytes((uint64_t)b->cams[i].width * b->cams[i].height) / 16;
@@ -1469,8 +1501,17 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
     }
     if (b->t.persistent) {
         hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, b->d_counter);
-        hipLaunchKernelGGL(pt_batch_kernel, dim3(b->grid_blocks), dim3(kBlock), 4u * (size_t)b->max_cwords, st,
-                           b->d_descs, b->d_items, b->n_items, b->d_counter);
+#define BATCH_LAUNCH(ACC, EN)                                                                                   \
+    hipLaunchKernelGGL((pt_batch_kernel<ACC, EN>), dim3(b->grid_blocks), dim3(kBlock), 4u * (size_t)b->max_cwords, st, \
+                       b->d_descs, b->d_items, b->n_items, b->d_counter)
+#define BATCH_LAUNCH_ENV(ACC)          \
+    if (b->env) BATCH_LAUNCH(ACC, true); \
+    else BATCH_LAUNCH(ACC, false)
+        if (b->indexed && b->wide) { BATCH_LAUNCH_ENV(IndexAccT<true>); }
+        else if (b->indexed) { BATCH_LAUNCH_ENV(IndexAccT<false>); }
+        else { BATCH_LAUNCH_ENV(VdbAcc); }
+#undef BATCH_LAUNCH_ENV
+#undef BATCH_LAUNCH
         if ((s = launch_check("batched render"))) return s;
         return batch_resolve(b, st);
     }
@@ -1481,14 +1522,18 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
         const uint32_t items = (uint32_t)(b->tiles_x[i] * b->tiles_y[i]) * g.chunks;
         hipLaunchKernelGGL(zero_u32, dim3(1), dim3(64), 0, st, b->d_counter);
         const dim3 grid(std::min<uint32_t>(items, (uint32_t)b->grid_blocks));
-        if (b->meds[i].env)
-            hipLaunchKernelGGL((pt_kernel<VdbAcc, VdbView, false, false, true>), grid, dim3(kBlock),
-                               4u * (size_t)g.cwords, st, b->views[i], b->cams[i], b->meds[i], g, b->majs[i],
-                               b->coarse[i], b->images[i], nullptr, nullptr, b->d_counter, b->sums[i], nullptr);
-        else
-            hipLaunchKernelGGL((pt_kernel<VdbAcc, VdbView, false, false, false>), grid, dim3(kBlock),
-                               4u * (size_t)g.cwords, st, b->views[i], b->cams[i], b->meds[i], g, b->majs[i],
-                               b->coarse[i], b->images[i], nullptr, nullptr, b->d_counter, b->sums[i], nullptr);
+#define VOLUME_LAUNCH(ACC, VIEW, FIELD, EN)                                                                       \
+    hipLaunchKernelGGL((pt_kernel<ACC, VIEW, false, false, EN>), grid, dim3(kBlock), 4u * (size_t)g.cwords, st, FIELD, \
+                       b->cams[i], b->meds[i], g, b->majs[i], b->coarse[i], b->images[i], nullptr, nullptr,        \
+                       b->d_counter, b->sums[i], nullptr)
+#define VOLUME_LAUNCH_ENV(ACC, VIEW, FIELD)                  \
+    if (b->meds[i].env) VOLUME_LAUNCH(ACC, VIEW, FIELD, true); \
+    else VOLUME_LAUNCH(ACC, VIEW, FIELD, false)
+        if (b->indexed && b->wide) { VOLUME_LAUNCH_ENV(IndexAccT<true>, IndexView, b->index[i].v); }
+        else if (b->indexed) { VOLUME_LAUNCH_ENV(IndexAccT<false>, IndexView, b->index[i].v); }
+        else { VOLUME_LAUNCH_ENV(VdbAcc, VdbView, b->views[i]); }
+#undef VOLUME_LAUNCH_ENV
+#undef VOLUME_LAUNCH
         if ((s = launch_check("per-volume render"))) return s;
     }
     return batch_resolve(b, st);
@@ -1505,9 +1550,9 @@ extern "C" vdbc_status vdbc_batch_workspace(const vdbc_batch_item* items, uint32
     vdbc_status s = batch_tuning(t, &tt);
     if (s) return s;
     vdbc_batch b;
-    std::vector<uint64_t> mo, co, so;
+    std::vector<uint64_t> mo, co, so, xo;
     uint64_t io, total;
-    if ((s = batch_plan(items, n, tt, &b, &mo, &co, &so, &io, &total))) return s;
+    if ((s = batch_plan(items, n, tt, &b, &mo, &co, &so, &xo, &io, &total))) return s;
     *bytes = total;
     return VDBC_OK;
 }
@@ -1524,9 +1569,9 @@ extern "C" vdbc_status vdbc_batch_create(const vdbc_batch_item* items, uint32_t 
     if (s) return s;
     std::unique_ptr<vdbc_batch> b(new (std::nothrow) vdbc_batch());
     if (!b) return fail(VDBC_E_NOMEM, "no memory");
-    std::vector<uint64_t> mo, co, so;
+    std::vector<uint64_t> mo, co, so, xo;
     uint64_t io, total;
-    if ((s = batch_plan(items, n, tt, b.get(), &mo, &co, &so, &io, &total))) return s;
+    if ((s = batch_plan(items, n, tt, b.get(), &mo, &co, &so, &xo, &io, &total))) return s;
     if (ws_bytes < total)
         return fail(VDBC_E_BUFFER_TOO_SMALL, "batch workspace needs %llu bytes", (unsigned long long)total);
     uint8_t* w = static_cast<uint8_t*>(ws);
@@ -1534,18 +1579,29 @@ extern "C" vdbc_status vdbc_batch_create(const vdbc_batch_item* items, uint32_t 
     b->d_descs = reinterpret_cast<BatchDesc*>(w + 256);
     b->d_cell_base = reinterpret_cast<uint32_t*>(w + 256 + align256((uint64_t)n * sizeof(BatchDesc)));
     b->d_coarse_base = b->d_cell_base + (n + 1);
+    b->d_index_base = b->d_coarse_base + (n + 1);
     b->d_items = reinterpret_cast<uint32_t*>(w + io);
     for (uint32_t i = 0; i < n; ++i) {
         b->majs.push_back(reinterpret_cast<float*>(w + mo[i]));
         b->coarse.push_back(reinterpret_cast<uint32_t*>(w + co[i]));
         b->sums.push_back(so[i] ? PtSums{reinterpret_cast<unsigned long long*>(w + so[i]), nullptr} : PtSums{});
     }
+    // twice where the first pass meets a volume that needs wide entries
+    b->index.resize(n);
+    b->indexed = true;
+    for (int pass = 0; pass < 2; ++pass)
+        for (uint32_t i = 0; i < n && b->indexed; ++i) {
+            b->indexed = make_index(&items[i].grid, b->views[i], reinterpret_cast<uint32_t*>(w + xo[i]), &b->index[i].v,
+                                    &b->wide);
+            b->index[i].wide = b->wide;
+        }
+    for (const MediumK& m : b->meds) b->env = b->env || m.env;
     // descriptors and the cost-ordered work list (largest estimated cost first:
     // samples per pixel x ray length through the volume)
     std::vector<BatchDesc> descs(n);
     std::vector<uint32_t> order(n);
     for (uint32_t i = 0; i < n; ++i) {
-        descs[i] = BatchDesc{b->views[i], b->cams[i], b->meds[i], b->gs[i], b->majs[i], b->coarse[i], b->images[i],
+        descs[i] = BatchDesc{b->views[i], b->index[i].v, b->cams[i], b->meds[i], b->gs[i], b->majs[i], b->coarse[i], b->images[i],
                              b->sums[i], b->tiles_x[i]};
         order[i] = i;
     }
@@ -1561,13 +1617,16 @@ extern "C" vdbc_status vdbc_batch_create(const vdbc_batch_item* items, uint32_t 
     // prefix tables of the batched majorant launches: macrocells and
     // coarse-bit workgroups per volume (the launch is used only while both
     // totals stay below 2^24 workgroups)
-    std::vector<uint32_t> bases(2 * (size_t)(n + 1), 0u);
+    std::vector<uint32_t> bases(3 * (size_t)(n + 1), 0u);
     for (uint32_t i = 0; i < n; ++i) {
         const PtArgs& g = b->gs[i];
         b->cells_total += (uint64_t)g.gx * g.gy * g.gz;
         b->cblocks_total += ((uint64_t)g.cgx * g.cgy * g.cgz + kBlock - 1) / kBlock;
         bases[i + 1] = (uint32_t)std::min<uint64_t>(b->cells_total, 0xFFFFFFFFull);
         bases[n + 1 + i + 1] = (uint32_t)std::min<uint64_t>(b->cblocks_total, 0xFFFFFFFFull);
+        const IndexView& iv = b->index[i].v;
+        if (b->indexed) b->iblocks_total += ((uint64_t)iv.tx * iv.ty * iv.tz + kBlock - 1) / kBlock;
+        bases[2 * (n + 1) + i + 1] = (uint32_t)std::min<uint64_t>(b->iblocks_total, 0xFFFFFFFFull);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (hipMemcpyAsync(b->d_cell_base, bases.data(), bases.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess ||

@@ -99,3 +99,31 @@ def test_buffer_past_4_gb_takes_wide_entries():
     want = _plain(r)
     assert np.array_equal(_bits(r.launch()), want)
     assert float(r.image[..., 3].max()) > 0.0
+
+
+@pytest.mark.parametrize("persistent", [1, 0])
+@pytest.mark.parametrize("env", [False, True])
+def test_batch_reads_its_volumes_through_their_indexes(persistent, env):
+    # volumes of every kind in one plan, bit-identical to single launches of
+    # the tree accessor; an environment map on one of them only
+    items, want = [], []
+    for i, name in enumerate(["ragged", "edge8", "one", "empty", "tiles", "partial"]):
+        v, rate, kw = _volume(name)
+        g = vdbc.Grid(vdbc.encode(v, rate, **kw)[0])
+        cam = scenes.orbit_camera(g.dims, 33 + i, 20, azimuth_deg=40.0 * i)
+        med = dict(scenes.pt_medium_tf5(32.0))
+        if env and i == 2:
+            med["env"] = torch.rand((4, 8, 3), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+        it = dict(grid=g, camera=cam, medium=med, spp=3, max_bounces=5, seed=50 + i, frame=i)
+        items.append(it)
+        prm = dict(spp=3, max_bounces=5, seed=50 + i, frame=i, macrocell=16, flags=vdbc.RENDER_CACHE_LEAF)
+        want.append(_bits(vdbc.render(g, cam, med, prm, vdbc.MODE_PT)))
+    b = vdbc.Batch(items, dict(persistent=persistent, chunk_spp=2))
+    for _ in range(2):
+        for img in b.images:
+            img.fill_(-1.0)
+        b.launch()
+        torch.cuda.synchronize()
+        for img, w in zip(b.images, want):
+            assert np.array_equal(_bits(img), w)
+    b.close()
