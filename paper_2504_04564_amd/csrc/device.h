@@ -304,8 +304,9 @@ struct IndexAccT {
     }
     __device__ __forceinline__ uint32_t table_offset(int i, int j, int k) const
     {
-        return 4u * ((uint32_t)((i + 8) >> 3) +
-                     (uint32_t)v.tx * ((uint32_t)((j + 8) >> 3) + (uint32_t)v.ty * (uint32_t)((k + 8) >> 3)));
+        // rows and row lengths below 2^24: 24-bit products
+        const uint32_t row = __umul24((uint32_t)((k + 8) >> 3), (uint32_t)v.ty) + (uint32_t)((j + 8) >> 3);
+        return 4u * (__umul24(row, (uint32_t)v.tx) + (uint32_t)((i + 8) >> 3));
     }
     __device__ __forceinline__ void corners(int i, int j, int k, float c[8])
     {
@@ -386,9 +387,9 @@ __device__ __forceinline__ float lerp(float a, float b, float t) { return fmaf(t
 template <class Acc>
 __device__ __forceinline__ float trilinear(Acc& acc, float px, float py, float pz)
 {
-    px = fminf(fmaxf(px, -2.0f), (float)acc.v.nx + 1.0f);
-    py = fminf(fmaxf(py, -2.0f), (float)acc.v.ny + 1.0f);
-    pz = fminf(fmaxf(pz, -2.0f), (float)acc.v.nz + 1.0f);
+    px = __builtin_amdgcn_fmed3f(px, -2.0f, (float)acc.v.nx + 1.0f);   // NaN: -2
+    py = __builtin_amdgcn_fmed3f(py, -2.0f, (float)acc.v.ny + 1.0f);
+    pz = __builtin_amdgcn_fmed3f(pz, -2.0f, (float)acc.v.nz + 1.0f);
     const float fx0 = floorf(px), fy0 = floorf(py), fz0 = floorf(pz);
     const float fx = px - fx0, fy = py - fy0, fz = pz - fz0;
     float c[8];
@@ -401,9 +402,9 @@ __device__ __forceinline__ float trilinear(Acc& acc, float px, float py, float p
 template <class Acc>
 __device__ __forceinline__ float nearest(Acc& acc, float px, float py, float pz)
 {
-    px = fminf(fmaxf(px, -2.0f), (float)acc.v.nx + 1.0f);
-    py = fminf(fmaxf(py, -2.0f), (float)acc.v.ny + 1.0f);
-    pz = fminf(fmaxf(pz, -2.0f), (float)acc.v.nz + 1.0f);
+    px = __builtin_amdgcn_fmed3f(px, -2.0f, (float)acc.v.nx + 1.0f);   // NaN: -2
+    py = __builtin_amdgcn_fmed3f(py, -2.0f, (float)acc.v.ny + 1.0f);
+    pz = __builtin_amdgcn_fmed3f(pz, -2.0f, (float)acc.v.nz + 1.0f);
     const float fx0 = floorf(px), fy0 = floorf(py), fz0 = floorf(pz);
     const int i = (int)fx0 + ((px - fx0) >= 0.5f);
     const int j = (int)fy0 + ((py - fy0) >= 0.5f);

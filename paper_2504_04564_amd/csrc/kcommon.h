@@ -93,14 +93,16 @@ static inline vdbc_status make_view(const vdbc_grid* g, VdbView* v)
 }
 
 // Region-index geometry of a volume: entries per axis (a region on every side
-// of the volume) and bytes; 0 bytes where the table would pass 2^32.
+// of the volume) and bytes; 0 bytes where the table would pass 2^32 or its
+// rows 2^24 (the accessor's 24-bit products).
 static inline uint64_t index_dims(uint64_t nx, uint64_t ny, uint64_t nz, uint64_t t[3])
 {
     t[0] = (nx + 7) / 8 + 2;
     t[1] = (ny + 7) / 8 + 2;
     t[2] = (nz + 7) / 8 + 2;
     const double n = (double)t[0] * (double)t[1] * (double)t[2];
-    return n < (double)(1u << 30) ? align256(4ull * t[0] * t[1] * t[2]) : 0;
+    const bool rows = t[0] < (1u << 24) && t[1] < (1u << 24) && t[2] < (1u << 24) && t[1] * t[2] < (1u << 24);
+    return rows && n < (double)(1u << 30) ? align256(4ull * t[0] * t[1] * t[2]) : 0;
 }
 
 // The region index of grid g with its table at `tab`; false where the buffer

@@ -154,7 +154,8 @@ __device__ __forceinline__ void flight_begin(Flight& f, const PtArgs& g, int nx,
 __device__ __forceinline__ bool coarse_occupied(const uint32_t* bits, const PtArgs& g, int bx,
                                                 int by, int bz)
 {
-    const uint32_t i = (uint32_t)(bx + g.cgx * (by + g.cgy * bz));
+    // at most 2^18 blocks: 24-bit products
+    const uint32_t i = __umul24(__umul24((uint32_t)bz, (uint32_t)g.cgy) + (uint32_t)by, (uint32_t)g.cgx) + (uint32_t)bx;
     return (bits[i >> 5] >> (i & 31u)) & 1u;
 }
 
@@ -404,32 +405,30 @@ __device__ __forceinline__ void pt_tile(Acc& acc, int nx, int ny, int nz, const 
             if (!dead) ++nseg;
             begin = kFlying;
         }
-        bool path_done = dead;
-        if (!dead) {
-            // a turn takes at most walk + 1 draws in flight (walk outside a
-            // cell) and one for the accept test
-            const int left = (int)(rng.made - rng.d) - (f.incell ? 2 : 1);
-            const int tentative = flight_advance(f, maj, cbits, g, rng, min(kWalkCells, left), ncell);
-            if (tentative == kFlightYield) continue;
-            // the density at the tentative collision is taken here, after the walk
-            // loop, so that the lanes of a wave that reached one in different
-            // steps of the walk sample in one pass
-            float sv = 0.0f;
-            if (tentative) {
-                sv = trilinear(acc, fmaf(f.t, f.d[0], f.o[0]), fmaf(f.t, f.d[1], f.o[1]), fmaf(f.t, f.d[2], f.o[2]));
-                ++nsamp;
-            }
-            const bool hit = tentative && rng.next() * f.mu < m.ds * tf_alpha_at(tf_lds, m, sv);
-            if (tentative && !hit) continue;    // null collision: keep tracking
+        // No way out of the middle of a turn from here on: the path's state
+        // stays in place under flags.  A turn takes at most walk + 1 draws in
+        // flight (walk outside a cell) and one for the accept test.
+        f.ok = f.ok && !dead;
+        const int left = (int)(rng.made - rng.d) - (f.incell ? 2 : 1);
+        const int tentative = flight_advance(f, maj, cbits, g, rng, min(kWalkCells, left), ncell);
+        // the density at the tentative collision is taken here, after the walk
+        // loop, so that the lanes of a wave that reached one in different
+        // steps of the walk sample in one pass
+        bool hit = false, path_done = dead;
+        float sv = 0.0f;
+        if (tentative == 1) {
+            sv = trilinear(acc, fmaf(f.t, f.d[0], f.o[0]), fmaf(f.t, f.d[1], f.o[1]), fmaf(f.t, f.d[2], f.o[2]));
+            ++nsamp;
+            hit = rng.next() * f.mu < m.ds * tf_alpha_at(tf_lds, m, sv);   // else a null collision: keep tracking
+        }
+        if (!dead && (hit || tentative == 0)) {
             if (!shadow) {
                 if (b == 0) {
                     phit = hit;
                     if (AOV) pdepth = hit ? (f.t - t0p) / (f.t1 - t0p) : 1.0f;
                 }
                 if (hit) {
-                    // real collision: weight by albedo and colour, then the
-                    // shadow ray towards the light from the collision point
-                    const float4 c = tf_eval(m, sv);
+                    const float4 c = tf_eval_at(tf_lds, m, sv);
                     b0 *= m.albedo * c.x;
                     b1 *= m.albedo * c.y;
                     b2 *= m.albedo * c.z;
