@@ -749,9 +749,29 @@ static uint64_t pt_workspace(uint32_t C, int nx, int ny, int nz)
     return 256 + align256(majorant_bytes(C, nx, ny, nz)) + align256(4ull * g.cwords);
 }
 
-// A path-traced launch splits its tiles into several work items (and needs
-// the per-pixel sums after the occupancy bits) iff 0 < chunk_spp < spp.
-static bool pt_split(const vdbc_render_params* r) { return r->chunk_spp != 0 && r->chunk_spp < r->spp; }
+static uint64_t pt_tiles(uint64_t width, uint64_t height, uint64_t tw);
+
+// Samples per work item of a path-traced launch (= spp: its tiles are not
+// split): the caller's, or with VDBC_RENDER_SPLIT and none given the most that
+// leaves about kSplitItems items.  The card holds 1280 workgroups at once, and
+// with a few items each the last ones to end leave most of it idle, while an
+// item of few samples drains its own lanes more often: at 4 samples 512^2
+// pixels (1024 tiles) take 1.47 ms whole, 0.85 ms by one sample, 1.15 ms by
+// two; 1024^2 pixels (4096 tiles) 2.79 ms whole, 2.61 ms by two samples.  More
+// than kSplitItems tiles are never split.
+constexpr uint64_t kSplitItems = 6144;
+
+static uint32_t pt_chunk(const vdbc_render_params* r, const vdbc_camera* c)
+{
+    if (r->chunk_spp != 0) return std::min(r->chunk_spp, r->spp);
+    if (!(r->flags & VDBC_RENDER_SPLIT) || !c || r->spp < 2) return r->spp;
+    const uint64_t n = (uint64_t)r->spp * pt_tiles(c->width, c->height, r->tile_w == 0 ? 8 : r->tile_w) / kSplitItems;
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n, 1), r->spp);
+}
+
+// Whether the tiles are split into several work items (which needs the
+// per-pixel sums after the occupancy bits).
+static bool pt_split(const vdbc_render_params* r, const vdbc_camera* c) { return pt_chunk(r, c) < r->spp; }
 
 // Bytes of the per-pixel sums of a split launch: 32 (red, green, blue,
 // hits | escapes) + 8 (AOV depth) per pixel.
@@ -973,7 +993,8 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     {
         // the work-item queue counts in 32 bits
         const uint64_t tiles = pt_tiles((uint64_t)cam.width, (uint64_t)cam.height, r->tile_w == 0 ? 8 : r->tile_w);
-        const uint64_t per_tile = pt_split(r) ? (r->spp + r->chunk_spp - 1) / r->chunk_spp : 1;
+        const uint32_t chunk = pt_chunk(r, c);
+        const uint64_t per_tile = (r->spp + chunk - 1) / chunk;
         if (tiles * per_tile > 0xFFFFFFFFull)
             return fail(VDBC_E_INVALID, "more than 2^32 work items: raise chunk_spp");
     }
@@ -1002,8 +1023,8 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     g.seed_hi = (uint32_t)(r->seed >> 32);
     g.frame = r->frame;
     g.rr = (r->flags & VDBC_RENDER_RR) ? 1 : 0;
-    const bool split = pt_split(r);
-    g.chunk = split ? r->chunk_spp : r->spp;
+    const bool split = pt_split(r, c);
+    g.chunk = pt_chunk(r, c);
     g.chunks = (r->spp + g.chunk - 1) / g.chunk;
     uint32_t* coarse = reinterpret_cast<uint32_t*>(
         static_cast<uint8_t*>(ws) + 256 + align256(majorant_bytes(r->macrocell, v.nx, v.ny, v.nz)));
@@ -1091,8 +1112,12 @@ extern "C" vdbc_status vdbc_render_workspace(const vdbc_render_params* r, vdbc_d
         if (r->macrocell < 4 || r->macrocell > 64 || (r->macrocell & (r->macrocell - 1)))
             return fail(VDBC_E_INVALID, "macrocell must be 4, 8, 16, 32 or 64");
         *bytes = pt_workspace(r->macrocell, (int)d.nx, (int)d.ny, (int)d.nz);
-        if (pt_split(r)) {
-            if (!c) return fail(VDBC_E_INVALID, "0 < chunk_spp < spp: the workspace size needs the camera");
+        if (r->chunk_spp == 0 ? (r->flags & VDBC_RENDER_SPLIT) != 0 && r->spp > 1 : r->chunk_spp < r->spp) {
+            if (!c) return fail(VDBC_E_INVALID, "work split: the workspace size needs the camera");
+            if (r->chunk_spp == 0 && r->tile_w != 0 && r->tile_w != 8 && r->tile_w != 16 && r->tile_w != 32 && r->tile_w != 64)
+                return fail(VDBC_E_INVALID, "tile_w must be 0 (default 8), 8, 16, 32 or 64");
+        }
+        if (pt_split(r, c)) {
             *bytes += pt_sums_bytes((uint64_t)c->width * (uint64_t)c->height);
         }
         if (r->flags & VDBC_RENDER_COST_ORDER) {
@@ -1148,11 +1173,29 @@ static vdbc_status render_vdb(const vdbc_grid* g, const vdbc_camera* c, const vd
     return render_impl<VdbAcc>(v, c, m, r, image, aov, ws, ws_bytes, stream, ix);
 }
 
+// The parameters of a call with VDBC_RENDER_SPLIT taken back where the
+// workspace has no room for the pixel sums (it is a choice of the library's,
+// not a demand).
+static const vdbc_render_params* fit_split(const vdbc_render_params* r, vdbc_dims d, const vdbc_camera* c,
+                                           uint64_t ws_bytes, vdbc_render_params* whole)
+{
+    uint64_t need = 0;
+    if (!r || !(r->flags & VDBC_RENDER_SPLIT) || vdbc_render_workspace(r, d, c, &need) || need <= ws_bytes) return r;
+    *whole = *r;
+    whole->flags &= ~(uint32_t)VDBC_RENDER_SPLIT;
+    return whole;
+}
+
 extern "C" vdbc_status vdbc_render(const vdbc_grid* g, const vdbc_camera* c, const vdbc_medium* m,
                                    const vdbc_render_params* r, float* image, float* aov, void* ws,
                                    uint64_t ws_bytes, void* stream)
 {
     clear_error();
+    VdbView v;
+    vdbc_status s = make_view(g, &v);
+    if (s) return s;
+    vdbc_render_params whole;
+    r = fit_split(r, vdbc_dims{(uint32_t)v.nx, (uint32_t)v.ny, (uint32_t)v.nz}, c, ws_bytes, &whole);
     return render_vdb(g, c, m, r, image, aov, ws, ws_bytes, stream);
 }
 
@@ -1201,6 +1244,8 @@ extern "C" vdbc_status vdbc_render_noalloc(const vdbc_grid* g, const vdbc_camera
     vdbc_status s = make_view(g, &v);
     if (s) return s;
     vdbc_dims d{(uint32_t)v.nx, (uint32_t)v.ny, (uint32_t)v.nz};
+    vdbc_render_params whole;
+    r = fit_split(r, d, c, kScratchBytes, &whole);
     uint64_t need = 0;
     if ((s = vdbc_render_workspace(r, d, c, &need))) return s;
     if (need > kScratchBytes)
@@ -1221,6 +1266,8 @@ extern "C" vdbc_status vdbc_render_dense(const float* dense, vdbc_dims d, float 
     DenseView v;
     vdbc_status s = make_dense(dense, d, background, &v);
     if (s) return s;
+    vdbc_render_params whole;
+    r = fit_split(r, d, c, ws_bytes, &whole);
     return render_impl<DenseAcc>(v, c, m, r, image, aov, ws, ws_bytes, stream);
 }
 

@@ -20,7 +20,7 @@ OK, E_INVALID, E_NOMEM, E_BUFFER_TOO_SMALL, E_FORMAT, E_DEVICE, E_UNSUPPORTED = 
 BG_EXPLICIT, NO_CORNERS, NO_PRUNE, PARTIAL = 1, 2, 4, 8
 MODE_EA, MODE_PT, MODE_ISO = 0, 1, 2
 RENDER_HDDA, RENDER_COUNT, RENDER_KEEP_MAJORANT, RENDER_RR = 1, 2, 4, 8
-RENDER_CACHE_NONE, RENDER_CACHE_LEAF, RENDER_COST_ORDER, RENDER_INDEX = 16, 32, 64, 128
+RENDER_CACHE_NONE, RENDER_CACHE_LEAF, RENDER_COST_ORDER, RENDER_INDEX, RENDER_SPLIT = 16, 32, 64, 128, 256
 # accessor cache policy -> render flag (2 = last leaf and last lower node, the default)
 CACHE_FLAGS = {0: RENDER_CACHE_NONE, 1: RENDER_CACHE_LEAF, 2: 0}
 # node layouts (bits): Morton child-slot order, SoA node words
@@ -391,6 +391,8 @@ class Renderer:
         # accessor cache policy is asked for
         if not self.dense and not self.prm.flags & (RENDER_CACHE_NONE | RENDER_CACHE_LEAF):
             self.prm.flags |= RENDER_INDEX
+        if mode == MODE_PT and self.prm.chunk_spp == 0:   # the library's choice of samples per work item
+            self.prm.flags |= RENDER_SPLIT
         ws = C.c_uint64(0)
         _check(load().vdbc_render_workspace(C.byref(self.prm), self.dims, C.byref(self.cam), C.byref(ws)))
         self.ws = torch.zeros(max(int(ws.value), 256) + 256, dtype=torch.uint8, device=device)
