@@ -101,6 +101,20 @@ struct VdbView {
 __device__ __forceinline__ uint32_t popc64(uint64_t x) { return __popcll(x); }
 __device__ __forceinline__ uint64_t below(uint32_t bit) { return (uint64_t(1) << bit) - 1u; }
 
+// The first 16 bytes of a word record, in one load (the empty statement keeps
+// the compiler from loading the mask and, once its bit is known, the indexes).
+struct WordHead {
+    uint64_t child;
+    uint32_t child_index, tile_index;
+};
+__device__ __forceinline__ WordHead word_head(const Word* w)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 q = *reinterpret_cast<const u32x4*>(w);
+    asm volatile("" : "+v"(q));
+    return WordHead{((uint64_t)q.y << 32) | q.x, q.z, q.w};
+}
+
 // What a VDB accessor keeps between consecutive lookups of one thread: nothing
 // (every lookup descends from the root), the last leaf region, or the last
 // leaf region and the last lower node.  The policy changes only the work of a
@@ -144,13 +158,13 @@ struct VdbAccT {
         const uint32_t n1 = (Lx & 31) + 32u * ((Ly & 31) + 32u * (Lz & 31));
         const Word* w = v.upper + (uint64_t)u * kUpperWords + (n1 >> 6);
         const uint32_t bit = n1 & 63u;
-        const uint64_t child = w->child;
-        if ((child >> bit) & 1u) {
-            cnode = v.lower + (uint64_t)(w->child_index + popc64(child & below(bit))) * kLowerWords;
+        const WordHead q = word_head(w);
+        if ((q.child >> bit) & 1u) {
+            cnode = v.lower + (uint64_t)(q.child_index + popc64(q.child & below(bit))) * kLowerWords;
             return;
         }
         const uint64_t tile = w->tile;
-        if ((tile >> bit) & 1u) cconst = v.upper_tiles + w->tile_index + popc64(tile & below(bit));
+        if ((tile >> bit) & 1u) cconst = v.upper_tiles + q.tile_index + popc64(tile & below(bit));
     }
 
     // Region of leaf (lx,ly,lz); negative coordinates and regions without a
@@ -168,15 +182,14 @@ struct VdbAccT {
                 const uint32_t n2 = (lx & 15) + 16u * ((ly & 15) + 16u * (lz & 15));
                 const Word* w = cnode + (n2 >> 6);
                 const uint32_t bit = n2 & 63u;
-                const uint64_t child = w->child;
-                if ((child >> bit) & 1u) {
-                    h.p = v.leaf_values +
-                          (uint64_t)(w->child_index + popc64(child & below(bit))) * kLeafVoxels;
+                const WordHead q = word_head(w);
+                if ((q.child >> bit) & 1u) {
+                    h.p = v.leaf_values + (uint64_t)(q.child_index + popc64(q.child & below(bit))) * kLeafVoxels;
                     h.m = 511u;
                 } else {
                     const uint64_t tile = w->tile;
                     if ((tile >> bit) & 1u)
-                        h.p = v.lower_tiles + w->tile_index + popc64(tile & below(bit));
+                        h.p = v.lower_tiles + q.tile_index + popc64(tile & below(bit));
                 }
             }
         }
