@@ -58,6 +58,13 @@ __device__ __forceinline__ void block_count(uint32_t n, unsigned long long* coun
     if (threadIdx.x == 0 && s) atomicAdd(counter, (unsigned long long)s);
 }
 
+// Orders the LDS of one wave, written and read by its own lanes only.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- host helpers
 
 static inline vdbc_status launch_check(const char* what)

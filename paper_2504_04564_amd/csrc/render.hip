@@ -20,82 +20,135 @@ __global__ void zero_u64(unsigned long long* p)
 
 // ---------------------------------------------------------------- majorant
 
-// One workgroup per macrocell: min and max of the values of the (C+2)^3
-// dilated footprint, reduced across the workgroup.  A dense array is read
-// voxel by voxel (thread -> z-column).  A VDB is read leaf region by leaf
-// region (thread -> 8^3 block of the footprint): a tile or an empty region
-// gives its one value without touching its voxels, a stored leaf its values
-// inside the footprint, so the empty space that makes up most of a
-// compressed volume costs one lookup per 512 voxels.  Both give the min and
-// max of the same values (the reconstruction, B outside), so the grids are
-// identical.
-// Leaf blocks a macrocell footprint can touch: (C + 2) / 8 + 2 per axis at
-// the largest macrocell, 64.
-constexpr int kMajorantQueue = 11 * 11 * 11;
+// A macrocell's majorant is ds times the largest alpha over [min, max] of the
+// values of its (C+2)^3 dilated footprint (the reconstruction, B outside).
 
-// The majorant of macrocell `cell` of a gx x gy x .. grid, by the whole
-// workgroup; thread 0 writes it.
-template <class Acc>
-__device__ void majorant_cell(Acc& acc, const MediumK& m, int C, int gx, int gy, uint32_t cell,
-                              float* __restrict__ out)
+// max of the piecewise-linear alpha over [vmin, vmax]: the two ends and every
+// control point strictly inside.
+__device__ __forceinline__ float majorant_of(const MediumK& m, float vmin, float vmax)
 {
+    float a = fmaxf(tf_alpha(m, vmin), tf_alpha(m, vmax));
+    const float p0 = (vmin - m.tf_lo) * m.tf_inv, p1 = (vmax - m.tf_lo) * m.tf_inv;
+    for (int q = 0; q < m.tf_n; ++q)
+        if ((float)q > p0 && (float)q < p1) a = fmaxf(a, m.tf[q].w);
+    return m.ds * a;
+}
+
+// VDB.  The 8^3 blocks of the footprint (at most 11^3, for a macrocell of 64;
+// 4^3 up to 16) are resolved one per thread: a tile or an empty region enters
+// the min and max at once, a stored leaf is queued in LDS, whole leaves at the
+// front and the slices of a border at the back.  A whole leaf is two 16-byte
+// loads a lane, two leaves at a time; eight borders, 64 values or fewer each,
+// are read at a time.  Up to macrocells of 16 a wave takes one each: such a
+// cell is a few latencies long, and a workgroup left three waves idle while
+// one resolved.  (One leaf at a time, eight masked 4-byte loads for a border
+// too: 186 us at 512^3 with cells of 16, 702 us at 994x676x1225 with 64.)
+constexpr int kMajorantQueue = 11 * 11 * 11;
+constexpr int kMajorantWaveCell = 16;
+
+struct MajorantShared {
+    const float* leaf[kMajorantQueue];
+    uint32_t box[kMajorantQueue];   // first voxel and extent - 1 per axis, 3 bits each
+    int n[kBlock / 64][2];
+    float red[2][kBlock / 64];
+};
+
+// Macrocell `cell` by a wave (WAVE) or by the workgroup.
+template <bool WAVE>
+__device__ __forceinline__ void majorant_tree(const VdbView& view, const MediumK& m, int C, int gx, int gy,
+                                              uint32_t cell, float* __restrict__ out, MajorantShared& sh)
+{
+    constexpr int T = WAVE ? 64 : kBlock, W = T / 64, N = WAVE ? 64 : kMajorantQueue;
+    constexpr uint32_t kWhole = 0x3FE00u;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tid = WAVE ? lane : (int)threadIdx.x, w0 = WAVE ? 0 : wave;
+    const float** const qleaf = sh.leaf + (WAVE ? 64 * wave : 0);
+    uint32_t* const qbox = sh.box + (WAVE ? 64 * wave : 0);
+    int* const qn = sh.n[WAVE ? wave : 0];
     const int cx = (int)(cell % (uint32_t)gx), cy = (int)((cell / (uint32_t)gx) % (uint32_t)gy),
               cz = (int)(cell / ((uint32_t)gx * (uint32_t)gy));
     const int E = C + 2, x0 = C * cx - 1, y0 = C * cy - 1, z0 = C * cz - 1;
     float vmin = INFINITY, vmax = -INFINITY;
-    if constexpr (Acc::kTree) {
-        // leaf blocks [bx0, bx0 + nbx) x ... covering the footprint (floor
-        // division; at most 11^3 for a macrocell of 64).  First every thread
-        // resolves its blocks: a constant region enters the min and max at
-        // once, a stored leaf is queued in LDS.  Then each wave reads the
-        // queued leaves whole, 8 voxels per lane, keeping those inside the
-        // footprint.
-        __shared__ const float* qleaf[kMajorantQueue];
-        __shared__ int qblock[kMajorantQueue];
-        __shared__ int qn;
-        if (threadIdx.x == 0) qn = 0;
-        __syncthreads();
-        const int bx0 = x0 >> 3, by0 = y0 >> 3, bz0 = z0 >> 3;
-        const int nbx = ((x0 + E - 1) >> 3) - bx0 + 1, nby = ((y0 + E - 1) >> 3) - by0 + 1,
-                  nbz = ((z0 + E - 1) >> 3) - bz0 + 1;
-        for (int b = threadIdx.x; b < nbx * nby * nbz; b += kBlock) {
-            const int lx = bx0 + b % nbx, ly = by0 + (b / nbx) % nby, lz = bz0 + b / (nbx * nby);
-            const LeafH h = acc.resolve(lx, ly, lz);
-            if (h.m == 0u) {
-                vmin = fminf(vmin, h.p[0]);
-                vmax = fmaxf(vmax, h.p[0]);
-            } else {
-                const int q = atomicAdd(&qn, 1);
-                qleaf[q] = h.p;
-                qblock[q] = b;
-            }
+    if (tid < 2) qn[tid] = 0;
+    if (WAVE) wave_lds_fence();
+    else __syncthreads();
+    VdbAccT<kCacheNone> acc{view};
+    acc.reset();
+    const int bx0 = x0 >> 3, by0 = y0 >> 3, bz0 = z0 >> 3;
+    const int nbx = ((x0 + E - 1) >> 3) - bx0 + 1, nby = ((y0 + E - 1) >> 3) - by0 + 1,
+              nbz = ((z0 + E - 1) >> 3) - bz0 + 1;
+    for (int b = tid; b < nbx * nby * nbz; b += T) {
+        const int l[3] = {bx0 + b % nbx, by0 + (b / nbx) % nby, bz0 + b / (nbx * nby)};
+        const LeafH h = acc.resolve(l[0], l[1], l[2]);
+        if (h.m == 0u) {
+            vmin = fminf(vmin, h.p[0]);
+            vmax = fmaxf(vmax, h.p[0]);
+            continue;
         }
-        __syncthreads();
-        const int lane = threadIdx.x & 63, nq = qn;
-        for (int q = threadIdx.x >> 6; q < nq; q += kBlock / 64) {
-            const int b = qblock[q];
-            const int ox = 8 * (bx0 + b % nbx) - x0, oy = 8 * (by0 + (b / nbx) % nby) - y0,
-                      oz = 8 * (bz0 + b / (nbx * nby)) - z0;
-            const float* p = qleaf[q];
+        const int c0[3] = {x0, y0, z0};
+        uint32_t box = 0;
+        int bits = 0;
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const int n3 = lane + 64 * s;
-                const int i = ox + (n3 & 7), j = oy + ((n3 >> 3) & 7), k = oz + (n3 >> 6);
-                if ((unsigned)i < (unsigned)E && (unsigned)j < (unsigned)E && (unsigned)k < (unsigned)E) {
-                    const float v = p[n3];
-                    vmin = fminf(vmin, v);
-                    vmax = fmaxf(vmax, v);
-                }
+        for (int a = 0; a < 3; ++a) {
+            const int lo = max(0, c0[a] - 8 * l[a]), n1 = min(7, c0[a] + E - 1 - 8 * l[a]) - lo;
+            box |= (uint32_t)lo << (3 * a) | (uint32_t)n1 << (9 + 3 * a);
+            bits += 32 - __clz(n1);
+        }
+        const int q = bits > 6 ? atomicAdd(&qn[0], 1) : N - 1 - atomicAdd(&qn[1], 1);
+        qleaf[q] = h.p;
+        qbox[q] = box;
+    }
+    if (WAVE) wave_lds_fence();
+    else __syncthreads();
+    const int nbig = qn[0], nsmall = qn[1];
+    for (int q = w0; q < nbig; q += 2 * W) {
+        const int q1 = min(q + W, nbig - 1);   // the same leaf twice at the end
+        const uint32_t box[2] = {qbox[q], qbox[q1]};
+        const float* p[2] = {qleaf[q], qleaf[q1]};
+        if (__all(box[0] == kWhole && box[1] == kWhole)) {
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const float4*>(p[u >> 1])[lane + 64 * (u & 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                vmin = fminf(fminf(fminf(vmin, v[u].x), fminf(v[u].y, v[u].z)), v[u].w);
+                vmax = fmaxf(fmaxf(fmaxf(vmax, v[u].x), fmaxf(v[u].y, v[u].z)), v[u].w);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float v[8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s) v[s] = p[u][lane + 64 * s];
+                const uint32_t i = (uint32_t)(lane & 7) - (box[u] & 7u), j = (uint32_t)(lane >> 3) - ((box[u] >> 3) & 7u);
+                const bool in = i <= ((box[u] >> 9) & 7u) && j <= ((box[u] >> 12) & 7u);
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+                    if (in && (uint32_t)s - ((box[u] >> 6) & 7u) <= (box[u] >> 15)) {
+                        vmin = fminf(vmin, v[s]);
+                        vmax = fmaxf(vmax, v[s]);
+                    }
             }
         }
-    } else {
-        for (int col = threadIdx.x; col < E * E; col += kBlock) {
-            const int i = col % E, j = col / E;
-            for (int k = 0; k < E; ++k) {
-                const float v = acc.voxel(x0 + i, y0 + j, z0 + k);
-                vmin = fminf(vmin, v);
-                vmax = fmaxf(vmax, v);
-            }
+    }
+    for (int q = w0; q < nsmall; q += 8 * W) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int at = N - 1 - min(q + u * W, nsmall - 1);
+            const uint32_t box = (uint32_t)__builtin_amdgcn_readfirstlane((int)qbox[at]);
+            const uint32_t nx = (box >> 9) & 7u, ny = (box >> 12) & 7u, nz = box >> 15;
+            const int sx = 32 - __clz((int)nx), sy = 32 - __clz((int)ny);
+            // lanes past the extents read its last voxels again
+            const uint32_t i = min((uint32_t)lane & ((1u << sx) - 1u), nx),
+                           j = min(((uint32_t)lane >> sx) & ((1u << sy) - 1u), ny),
+                           k = min((uint32_t)lane >> (sx + sy), nz);
+            v[u] = qleaf[at][(box & 0x1FFu) + i + 8u * j + 64u * k];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            vmin = fminf(vmin, v[u]);
+            vmax = fmaxf(vmax, v[u]);
         }
     }
 #pragma unroll
@@ -103,35 +156,137 @@ __device__ void majorant_cell(Acc& acc, const MediumK& m, int C, int gx, int gy,
         vmin = fminf(vmin, __shfl_xor(vmin, o));
         vmax = fmaxf(vmax, __shfl_xor(vmax, o));
     }
-    __shared__ float red[2][kBlock / 64];
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[0][w] = vmin;
-        red[1][w] = vmax;
+    if (!WAVE) {
+        if (lane == 0) {
+            sh.red[0][wave] = vmin;
+            sh.red[1][wave] = vmax;
+        }
+        __syncthreads();
+        if (threadIdx.x != 0) return;
+        for (int q = 1; q < W; ++q) {
+            vmin = fminf(vmin, sh.red[0][q]);
+            vmax = fmaxf(vmax, sh.red[1][q]);
+        }
     }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (int q = 1; q < kBlock / 64; ++q) {
-        vmin = fminf(vmin, red[0][q]);
-        vmax = fmaxf(vmax, red[1][q]);
-    }
-    // max of the piecewise-linear alpha over [vmin, vmax]: the two ends and
-    // every control point strictly inside
-    float a = fmaxf(tf_alpha(m, vmin), tf_alpha(m, vmax));
-    const float p0 = (vmin - m.tf_lo) * m.tf_inv, p1 = (vmax - m.tf_lo) * m.tf_inv;
-    for (int q = 0; q < m.tf_n; ++q)
-        if ((float)q > p0 && (float)q < p1) a = fmaxf(a, m.tf[q].w);
-    out[cell] = m.ds * a;
+    if (tid == 0) out[cell] = majorant_of(m, vmin, vmax);
 }
 
-template <class Acc, class View>
-__global__ __launch_bounds__(kBlock) void majorant_kernel(View view, MediumK m, int C, int gx,
-                                                          int gy, int gz, float* __restrict__ out)
+// Workgroup `blk` of a volume's majorants (majorant_groups of them).
+__device__ __forceinline__ void majorant_tree_group(const VdbView& view, const MediumK& m, int C, int gx, int gy, int gz,
+                                                    uint32_t blk, float* __restrict__ out)
 {
-    (void)gz;
-    Acc acc{view};
-    acc.reset();
-    majorant_cell(acc, m, C, gx, gy, blockIdx.x, out);
+    __shared__ MajorantShared sh;
+    if (C <= kMajorantWaveCell) {
+        const uint32_t cell = blk * (kBlock / 64) + (threadIdx.x >> 6);
+        if (cell < (uint32_t)gx * (uint32_t)gy * (uint32_t)gz) majorant_tree<true>(view, m, C, gx, gy, cell, out, sh);
+    } else {
+        majorant_tree<false>(view, m, C, gx, gy, blk, out, sh);
+    }
+}
+
+static uint64_t majorant_groups(int C, uint64_t cells)
+{
+    return C <= kMajorantWaveCell ? (cells + kBlock / 64 - 1) / (kBlock / 64) : cells;
+}
+
+__global__ __launch_bounds__(kBlock) void majorant_tree_kernel(VdbView view, MediumK m, int C, int gx, int gy, int gz,
+                                                               float* __restrict__ out)
+{
+    majorant_tree_group(view, m, C, gx, gy, gz, blockIdx.x, out);
+}
+
+// Dense array.  A workgroup takes a run of macrocells along x, 256 voxels at
+// most: a lane reads its column of the run's (C+2)^2 rows (256 contiguous bytes
+// a wave and row), six rows in flight; the cells fold the columns in LDS.  The
+// columns before and after the run are read by all threads, a row each.  Bound
+// by the array's bytes, (C+2)^2 / C^2 times.  (A thread per row of a cell's own
+// footprint read 72-byte rows, column by column: 364 us at 512^3, cells of 16.)
+__global__ __launch_bounds__(kBlock) void majorant_dense_kernel(DenseView view, MediumK m, int C, int gx, int gy,
+                                                                int run, int runs, float* __restrict__ out)
+{
+    __shared__ float col[2][kBlock + 2][4];   // min, max of the run's columns, from the one before it; by row set
+    __shared__ float ends[2][2][kBlock / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int width = run * C, chunks = (width + 63) / 64, sets = chunks == 1 ? 4 : chunks == 2 ? 2 : 1;
+    const int rx = (int)(blockIdx.x % (unsigned)runs), cy = (int)((blockIdx.x / (unsigned)runs) % (unsigned)gy),
+              cz = (int)(blockIdx.x / ((unsigned)runs * (unsigned)gy));
+    const int E = C + 2, x0 = rx * width, y0 = C * cy - 1, z0 = C * cz - 1;
+    const int64_t sy = view.nx, sz = (int64_t)view.nx * view.ny;
+    const float B = view.background;
+    // rows outside the volume read B; in its place one of the footprint's own
+    // rows is read again and B enters below
+    const bool rows_out = y0 < 0 || z0 < 0 || y0 + E > view.ny || z0 + E > view.nz;
+    const int chunk = sets == 4 ? 0 : sets == 2 ? wave & 1 : wave, set = sets == 4 ? wave : sets == 2 ? wave >> 1 : 0;
+    const int c = 64 * chunk + lane, x = x0 + c;
+    float vmin = rows_out ? B : INFINITY, vmax = rows_out ? B : -INFINITY;
+    if (chunk < chunks && x < view.nx) {
+        const float* const base = view.data + x;
+        const int nj = (E + sets - 1) / sets;
+        for (int k = 0; k < E; ++k) {
+            const float* const plane = base + sz * min(max(z0 + k, 0), view.nz - 1);
+            for (int j = 0; j < nj; j += 6) {
+                float v[6];
+#pragma unroll
+                for (int u = 0; u < 6; ++u) {
+                    const int row = min((j + u) * sets + set, E - 1);
+                    v[u] = plane[sy * min(max(y0 + row, 0), view.ny - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < 6; ++u) {
+                    vmin = fminf(vmin, v[u]);
+                    vmax = fmaxf(vmax, v[u]);
+                }
+            }
+        }
+    } else {
+        vmin = vmax = B;
+    }
+    if (chunk < chunks) {
+        col[0][c + 1][set] = vmin;
+        col[1][c + 1][set] = vmax;
+    }
+    // the columns x0 - 1 and x0 + width
+    float e0[2] = {INFINITY, INFINITY}, e1[2] = {-INFINITY, -INFINITY};
+    for (int r = t; r < E * E; r += kBlock) {
+        const int64_t row = sy * min(max(y0 + r % E, 0), view.ny - 1) + sz * min(max(z0 + r / E, 0), view.nz - 1);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int xe = s ? x0 + width : x0 - 1;
+            const float v = xe < 0 || xe >= view.nx ? B : view.data[row + xe];
+            e0[s] = fminf(e0[s], v);
+            e1[s] = fmaxf(e1[s], v);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            e0[s] = fminf(e0[s], __shfl_xor(e0[s], o));
+            e1[s] = fmaxf(e1[s], __shfl_xor(e1[s], o));
+        }
+    if (lane == 0)
+        for (int s = 0; s < 2; ++s) {
+            ends[0][s][wave] = e0[s];
+            ends[1][s][wave] = e1[s];
+        }
+    __syncthreads();
+    const int cx = rx * run + t;
+    if (t >= run || cx >= gx) return;
+    float lo = rows_out ? B : INFINITY, hi = rows_out ? B : -INFINITY;
+    for (int q = C * t; q < C * t + E; ++q) {
+        if (q == 0 || q == width + 1) {
+            for (int w = 0; w < kBlock / 64; ++w) {
+                lo = fminf(lo, ends[0][q != 0][w]);
+                hi = fmaxf(hi, ends[1][q != 0][w]);
+            }
+        } else {
+            for (int w = 0; w < sets; ++w) {
+                lo = fminf(lo, col[0][q][w]);
+                hi = fmaxf(hi, col[1][q][w]);
+            }
+        }
+    }
+    out[(uint32_t)cx + (uint32_t)gx * ((uint32_t)cy + (uint32_t)gy * (uint32_t)cz)] = majorant_of(m, lo, hi);
 }
 
 // ---------------------------------------------------------------- region index
@@ -810,16 +965,39 @@ static vdbc_status launch_index(const VdbView& v, const IndexPlan& ix, hipStream
     return launch_check("region index");
 }
 
-template <class Acc, class View>
-static vdbc_status launch_majorant(const View& v, const MediumK& m, uint32_t C, float* out,
-                                   hipStream_t st)
+static vdbc_status majorant_cells(int nx, int ny, int nz, uint32_t C, int g[3], uint64_t* cells)
 {
-    const int gx = (v.nx + C - 1) / C, gy = (v.ny + C - 1) / C, gz = (v.nz + C - 1) / C;
-    const uint64_t cells = (uint64_t)gx * gy * gz;
     if (C < 4 || C > 64) return fail(VDBC_E_INVALID, "macrocell must be in [4, 64]");   // sizes kMajorantQueue
-    if (cells > 0x7FFFFFFFull) return fail(VDBC_E_INVALID, "too many macrocells (%llu)", (unsigned long long)cells);
-    hipLaunchKernelGGL((majorant_kernel<Acc, View>), dim3((unsigned)cells), dim3(kBlock), 0, st, v, m,
-                       (int)C, gx, gy, gz, out);
+    g[0] = (int)(((int64_t)nx + C - 1) / C);
+    g[1] = (int)(((int64_t)ny + C - 1) / C);
+    g[2] = (int)(((int64_t)nz + C - 1) / C);
+    *cells = (uint64_t)g[0] * g[1] * g[2];
+    if (*cells > 0x7FFFFFFFull)
+        return fail(VDBC_E_INVALID, "too many macrocells (%llu)", (unsigned long long)*cells);
+    return VDBC_OK;
+}
+
+static vdbc_status launch_majorant(const VdbView& v, const MediumK& m, uint32_t C, float* out, hipStream_t st)
+{
+    int g[3];
+    uint64_t cells;
+    vdbc_status s = majorant_cells(v.nx, v.ny, v.nz, C, g, &cells);
+    if (s) return s;
+    hipLaunchKernelGGL(majorant_tree_kernel, dim3((unsigned)majorant_groups((int)C, cells)), dim3(kBlock), 0, st, v, m,
+                       (int)C, g[0], g[1], g[2], out);
+    return launch_check("majorant");
+}
+
+static vdbc_status launch_majorant(const DenseView& v, const MediumK& m, uint32_t C, float* out, hipStream_t st)
+{
+    int g[3];
+    uint64_t cells;
+    vdbc_status s = majorant_cells(v.nx, v.ny, v.nz, C, g, &cells);
+    if (s) return s;
+    // 64, 128 or 256 voxels of cells: narrow volumes leave no wave idle
+    const int width = v.nx <= 64 ? 64 : v.nx <= 128 ? 128 : 256, run = width / (int)C, runs = (g[0] + run - 1) / run;
+    hipLaunchKernelGGL(majorant_dense_kernel, dim3((unsigned)runs * (unsigned)g[1] * (unsigned)g[2]), dim3(kBlock), 0, st,
+                       v, m, (int)C, g[0], g[1], run, runs, out);
     return launch_check("majorant");
 }
 
@@ -1010,7 +1188,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     if ((s = launch_check("zero counters"))) return s;
     float* maj = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + 256);
     if (!(r->flags & VDBC_RENDER_KEEP_MAJORANT)) {
-        s = launch_majorant<Acc>(v, m, r->macrocell, maj, st);
+        s = launch_majorant(v, m, r->macrocell, maj, st);
         if (s) return s;
     }
     PtArgs g;
@@ -1282,7 +1460,7 @@ extern "C" vdbc_status vdbc_majorant(const vdbc_grid* g, const vdbc_medium* med,
     if (C < 4 || C > 64) return fail(VDBC_E_INVALID, "macrocell must be in [4, 64]");
     MediumK m;
     if ((s = make_medium(med, v.nx, v.ny, v.nz, &m))) return s;
-    return launch_majorant<VdbAcc>(v, m, C, out, static_cast<hipStream_t>(stream));
+    return launch_majorant(v, m, C, out, static_cast<hipStream_t>(stream));
 }
 
 extern "C" vdbc_status vdbc_majorant_dense(const float* dense, vdbc_dims d, float background,
@@ -1297,7 +1475,7 @@ extern "C" vdbc_status vdbc_majorant_dense(const float* dense, vdbc_dims d, floa
     if (C < 4 || C > 64) return fail(VDBC_E_INVALID, "macrocell must be in [4, 64]");
     MediumK m;
     if ((s = make_medium(med, v.nx, v.ny, v.nz, &m))) return s;
-    return launch_majorant<DenseAcc>(v, m, C, out, static_cast<hipStream_t>(stream));
+    return launch_majorant(v, m, C, out, static_cast<hipStream_t>(stream));
 }
 
 // ---------------------------------------------------------------- batched majorants
@@ -1305,7 +1483,7 @@ extern "C" vdbc_status vdbc_majorant_dense(const float* dense, vdbc_dims d, floa
 // in one launch each, with the per-cell code of the single-volume kernels (so
 // the grids and bits are bitwise those of per-volume launches): workgroup b
 // belongs to the volume v with base[v] <= b < base[v + 1], a prefix table of
-// the volumes' macrocells (coarse-bit workgroups), and works on its local
+// the volumes' majorant (coarse-bit) workgroups, and works on its local
 // index b - base[v].  Small volumes no longer leave the chip idle one launch
 // at a time.
 
@@ -1330,9 +1508,8 @@ __global__ __launch_bounds__(kBlock) void majorant_batch_kernel(const BatchDesc*
     __syncthreads();
     const uint32_t v = s_v;
     const BatchDesc* D = descs + v;
-    VdbAcc acc{D->view};
-    acc.reset();
-    majorant_cell(acc, D->med, D->g.C, D->g.gx, D->g.gy, blockIdx.x - base[v], const_cast<float*>(D->maj));
+    majorant_tree_group(D->view, D->med, D->g.C, D->g.gx, D->g.gy, D->g.gz, blockIdx.x - base[v],
+                        const_cast<float*>(D->maj));
 }
 
 __global__ __launch_bounds__(kBlock) void index_batch_kernel(const BatchDesc* __restrict__ descs,
@@ -1373,10 +1550,10 @@ struct vdbc_batch {
     BatchDesc* d_descs = nullptr;
     uint32_t* d_items = nullptr;
     uint32_t* d_counter = nullptr;
-    uint32_t* d_cell_base = nullptr;     // prefix tables of macrocells and coarse-bit workgroups
+    uint32_t* d_cell_base = nullptr;     // prefix tables of majorant and coarse-bit workgroups
     uint32_t* d_coarse_base = nullptr;
     uint32_t* d_index_base = nullptr;    // ... and of index workgroups
-    uint64_t cells_total = 0, cblocks_total = 0, iblocks_total = 0;
+    uint64_t mblocks_total = 0, cblocks_total = 0, iblocks_total = 0;
     // region indexes of all volumes (in bytes, or wide where one of them
     // needs it), or of none where one cannot have any
     std::vector<IndexPlan> index;
@@ -1512,10 +1689,10 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
     // the persistent launch builds every volume's majorant grid and coarse
     // bits in one launch each (below the grid-size limit); one launch per
     // volume otherwise, and for the per-volume baseline
-    const bool batched_pre = b->t.persistent && b->cells_total < (1ull << 24) && b->cblocks_total < (1ull << 24) &&
+    const bool batched_pre = b->t.persistent && b->mblocks_total < (1ull << 24) && b->cblocks_total < (1ull << 24) &&
                              b->iblocks_total < (1ull << 24);
     if (batched_pre) {
-        hipLaunchKernelGGL(majorant_batch_kernel, dim3((unsigned)b->cells_total), dim3(kBlock), 0, st, b->d_descs,
+        hipLaunchKernelGGL(majorant_batch_kernel, dim3((unsigned)b->mblocks_total), dim3(kBlock), 0, st, b->d_descs,
                            b->d_cell_base, b->n);
         if ((s = launch_check("batched majorants"))) return s;
         hipLaunchKernelGGL(coarse_bits_batch_kernel, dim3((unsigned)b->cblocks_total), dim3(kBlock), 0, st,
@@ -1529,7 +1706,7 @@ static vdbc_status batch_enqueue(vdbc_batch* b, hipStream_t st)
     }
     for (uint32_t i = 0; i < b->n; ++i) {
         if (!batched_pre) {
-            if ((s = launch_majorant<VdbAcc>(b->views[i], b->meds[i], (uint32_t)b->gs[i].C, b->majs[i], st)))
+            if ((s = launch_majorant(b->views[i], b->meds[i], (uint32_t)b->gs[i].C, b->majs[i], st)))
                 return s;
             const PtArgs& g = b->gs[i];
             const uint64_t ncoarse = (uint64_t)g.cgx * g.cgy * g.cgz;
@@ -1667,9 +1844,9 @@ extern "C" vdbc_status vdbc_batch_create(const vdbc_batch_item* items, uint32_t 
     std::vector<uint32_t> bases(3 * (size_t)(n + 1), 0u);
     for (uint32_t i = 0; i < n; ++i) {
         const PtArgs& g = b->gs[i];
-        b->cells_total += (uint64_t)g.gx * g.gy * g.gz;
+        b->mblocks_total += majorant_groups(g.C, (uint64_t)g.gx * g.gy * g.gz);
         b->cblocks_total += ((uint64_t)g.cgx * g.cgy * g.cgz + kBlock - 1) / kBlock;
-        bases[i + 1] = (uint32_t)std::min<uint64_t>(b->cells_total, 0xFFFFFFFFull);
+        bases[i + 1] = (uint32_t)std::min<uint64_t>(b->mblocks_total, 0xFFFFFFFFull);
         bases[n + 1 + i + 1] = (uint32_t)std::min<uint64_t>(b->cblocks_total, 0xFFFFFFFFull);
         const IndexView& iv = b->index[i].v;
         if (b->indexed) b->iblocks_total += ((uint64_t)iv.tx * iv.ty * iv.tz + kBlock - 1) / kBlock;

@@ -39,13 +39,6 @@ __device__ __forceinline__ uint64_t region_word(const LeafH& h) { return reinter
 typedef const __attribute__((address_space(1))) float GlobalFloat;
 __device__ __forceinline__ GlobalFloat* region_values(uint64_t r) { return reinterpret_cast<GlobalFloat*>(r & ~1ull); }
 
-// The LDS of one wave, written and read by its own lanes only.
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __global__ __launch_bounds__(kBlock) void sample_tree_kernel(VdbView view, const float* __restrict__ pos, uint64_t n,
                                                              float* __restrict__ out)
 {
