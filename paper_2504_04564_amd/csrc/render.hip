@@ -939,9 +939,8 @@ static uint64_t pt_tiles(uint64_t width, uint64_t height, uint64_t tw)
     return pt_tiles_x(width, tw) * ((height + 64 / tw - 1) / (64 / tw));
 }
 
-// Bytes of the cost order (VDBC_RENDER_COST_ORDER): bin histogram and bin
-// offsets (kCostBins u32 each), then per tile its bin and its place in the
-// order (u32 each).
+// Bytes of the cost order (VDBC_RENDER_COST_ORDER): 2 kCostBins u32 unused,
+// then per tile its bin and the tile at its place in the order (u32 each).
 static uint64_t pt_order_bytes(uint64_t tiles) { return align256(8ull * kCostBins + 8ull * tiles); }
 
 // Region index of a VDB render (VDBC_RENDER_INDEX): its table follows the
@@ -1227,17 +1226,13 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     }
     const uint32_t* order = nullptr;
     if (r->flags & VDBC_RENDER_COST_ORDER) {
-        uint32_t* hist = reinterpret_cast<uint32_t*>(tail + (split ? pt_sums_bytes(npix) : 0));
-        uint32_t* off = hist + kCostBins;
-        uint32_t* key = off + kCostBins;
+        uint32_t* key = reinterpret_cast<uint32_t*>(tail + (split ? pt_sums_bytes(npix) : 0)) + 2 * kCostBins;
         uint32_t* ord = key + tiles;
-        const unsigned tb = (unsigned)((tiles + kBlock - 1) / kBlock);
-        hipLaunchKernelGGL(pt_sums_clear_kernel, dim3(1), dim3(kBlock), 0, st, reinterpret_cast<uint4*>(hist),
-                           (uint64_t)(2 * kCostBins / 4));
-        hipLaunchKernelGGL(pt_tile_cost_kernel, dim3(tb), dim3(kBlock), 0, st, cam, g, v.nx, v.ny, v.nz, maj,
-                           (uint32_t)pt_tiles_x((uint64_t)cam.width, (uint64_t)g.tw), (uint32_t)tiles, key, hist);
-        hipLaunchKernelGGL(pt_cost_offsets_kernel, dim3(1), dim3(64), 0, st, hist, off);
-        hipLaunchKernelGGL(pt_cost_scatter_kernel, dim3(tb), dim3(kBlock), 0, st, key, off, ord, (uint32_t)tiles);
+        constexpr uint64_t per_group = kBlock / kCostLanes;
+        hipLaunchKernelGGL(pt_tile_cost_kernel, dim3((unsigned)((tiles + per_group - 1) / per_group)), dim3(kBlock), 0, st, cam,
+                           g, v.nx, v.ny, v.nz, maj, (uint32_t)pt_tiles_x((uint64_t)cam.width, (uint64_t)g.tw),
+                           (uint32_t)tiles, key);
+        hipLaunchKernelGGL(pt_cost_order_kernel, dim3(1), dim3(1024), 0, st, key, ord, (uint32_t)tiles);
         if ((s = launch_check("cost order"))) return s;
         order = ord;
     }
