@@ -43,11 +43,13 @@ int wgrad_chunk(uint64_t P, int K)
 }
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-__device__ __forceinline__ uint16_t f2bf(float f)
+// Round to nearest even (v_cvt_pk_bf16_f32, one instruction for two values).
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);   // round to nearest even
-    return (uint16_t)(u >> 16);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
 }
 __device__ __forceinline__ bf16x8 load8(const uint16_t* p)
 {
@@ -199,22 +201,137 @@ __device__ __forceinline__ void fwd_store_staged(float* s_out, const f4 (&acc)[4
             }
         __syncthreads();
         const int c_lo = pass * PT * 16, c_hi = min(cout, c_lo + PT * 16);
-        const int groups = (c_hi - c_lo) / 4;
-        for (int e = threadIdx.x; e < kFwdTH * kFwdTW * groups; e += kThreads) {
-            const int p = e / groups, c = c_lo + (e - p * groups) * 4;
+        const auto store = [&](int p, int cl) {
+            const int c = c_lo + cl;
             const int y = ty0 + p / kFwdTW, x = tx0 + p % kFwdTW;
-            if (y >= ho || x >= wo) continue;
+            if (y >= ho || x >= wo) return;
             const int64_t pp = ((int64_t)n * ho + y) * wo + x;
-            uint16_t out[4];
+            float v[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                float v = s_out[(c - c_lo + j) * kEpiStride + p] + bias[c + j];
-                if (relu) v = fmaxf(v, 0.0f);
-                out[j] = f2bf(v);
+                v[j] = s_out[(cl + j) * kEpiStride + p] + bias[c + j];
+                if (relu) v[j] = fmaxf(v[j], 0.0f);
             }
-            *reinterpret_cast<uint2*>(out_bf + pp * cout + c) =
-                make_uint2((uint32_t)out[0] | (uint32_t)out[1] << 16, (uint32_t)out[2] | (uint32_t)out[3] << 16);
+            *reinterpret_cast<uint2*>(out_bf + pp * cout + c) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+        };
+        // full passes: a thread keeps its channels and takes every 32nd (64th) pixel
+        const int groups = (c_hi - c_lo) / 4;
+        if (groups == PT * 4) {
+            constexpr int G = PT * 4;
+            const int cl = ((int)threadIdx.x % G) * 4;
+#pragma unroll 4
+            for (int p = threadIdx.x / G; p < kFwdTH * kFwdTW; p += kThreads / G) store(p, cl);
+        } else {
+            for (int e = threadIdx.x; e < kFwdTH * kFwdTW * groups; e += kThreads) {
+                const int p = e / groups;
+                store(p, (e - p * groups) * 4);
+            }
         }
+    }
+}
+
+// Stages the n 16-byte groups of a pixel window, cg groups a pixel, into LDS
+// with one group of padding per pixel: load(pixel, group) gives a group.  Six
+// loads of a thread are in flight before the first is written (one by one, the
+// window of a 64-channel layer was eleven memory latencies long).
+template <class Load>
+__device__ __forceinline__ void stage_window(uint4* s_tile, int n, int cg, const Load& load)
+{
+    constexpr int U = 6;
+    const bool pow2 = (cg & (cg - 1)) == 0;
+    const int shift = 31 - __clz(cg);
+    for (int e0 = threadIdx.x; e0 < n; e0 += U * kThreads) {
+        uint4 v[U];
+        int at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = min(e0 + u * kThreads, n - 1);
+            const int pix = pow2 ? e >> shift : e / cg, c8 = e - pix * cg;
+            at[u] = pix * (cg + 1) + c8;
+            v[u] = load(pix, c8);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (e0 + u * kThreads < n) s_tile[at[u]] = v[u];
+    }
+}
+
+// The contraction of a stride-1 tile over its staged window (cin channels a
+// pixel), weights w[co][tap][c]: acc += window x w^T in chunks of 32 k; MIRROR:
+// tap (ky, kx) reads the window at (2 - ky, 2 - kx).  Channels past cout read
+// the last one's weights: their results are never stored.  With cin a multiple
+// of 32 a chunk lies in one tap: its offsets are scalar, the lanes' stay what
+// they are, and the weights are loaded up to three chunks ahead.  (Tap, channel
+// and address of every lane and chunk took some eighteen VALU instructions for
+// each MFMA.)
+template <int NT, bool MIRROR>
+__device__ __forceinline__ void conv_tile_accumulate(const uint4* s_tile, const uint16_t* __restrict__ w, int cin,
+                                                     int cout, f4 (&acc)[4][NT])
+{
+    constexpr int IW = kFwdTW + 2;
+    const int K = 9 * cin, ps = cin / 8 + 1;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
+    const int row0 = 2 * wave + (MIRROR ? 2 : 0), col0 = r + (MIRROR ? 2 : 0);
+    uint32_t b[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) b[t] = (uint32_t)(min(t * 16 + r, cout - 1) * K + 8 * g);
+    if (cin % 32 == 0) {
+        int a[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[m] = ((row0 + (m >> 1)) * IW + (m & 1) * 16 + col0) * ps + g;
+        // the chunks come in threes (9 cin / 32); four channel tiles have no
+        // registers for more than one ahead
+        constexpr int D = NT <= 2 ? 3 : 1;
+        bf16x8 Bn[D][NT];
+#pragma unroll
+        for (int u = 0; u < D; ++u)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) Bn[u][t] = load8(w + 32 * u + b[t]);
+        int c = 0, kx = 0, tap_off = 0;
+        for (int kb = 0; kb < K; kb += 32 * D) {
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                bf16x8 B[NT], A[4];
+                const int off = (MIRROR ? -tap_off : tap_off) + c / 8;
+#pragma unroll
+                for (int m = 0; m < 4; ++m) A[m] = __builtin_bit_cast(bf16x8, s_tile[a[m] + off]);
+                const uint16_t* const wn = w + min(kb + 32 * (u + D), K - 32);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    B[t] = Bn[u][t];
+                    Bn[u][t] = load8(wn + b[t]);
+                }
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[m][t] = mfma(A[m], B[t], acc[m][t]);
+                c += 32;
+                if (c == cin) {
+                    c = 0;
+                    tap_off += kx == 2 ? (IW - 2) * ps : ps;
+                    kx = kx == 2 ? 0 : kx + 1;
+                }
+            }
+        }
+        return;
+    }
+    for (int kb = 0; kb < K; kb += 32) {
+        const int k = kb + 8 * g;
+        const int tap = k / cin, c0 = k - tap * cin;
+        const bool valid = tap < 9;
+        const int ky = tap / 3, kx = tap - 3 * (tap / 3);
+        bf16x8 B[NT], A[4];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) B[t] = valid ? load8(w + b[t] + kb) : zero8();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int row = row0 + (m >> 1) + (MIRROR ? -ky : ky), col = (m & 1) * 16 + col0 + (MIRROR ? -kx : kx);
+            A[m] = valid ? __builtin_bit_cast(bf16x8, s_tile[(row * IW + col) * ps + c0 / 8]) : zero8();
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[m][t] = mfma(A[m], B[t], acc[m][t]);
     }
 }
 
@@ -227,14 +344,12 @@ __global__ __launch_bounds__(kThreads) void conv_fwd_tiled_kernel(ConvIn in, con
                                                                   const uint16_t* __restrict__ resid)
 {
     extern __shared__ uint4 s_tile[];
-    const int cin = in.ca + in.cb, K = 9 * cin, cg = cin / 8, ps = cg + 1;
+    const int cin = in.ca + in.cb, cg = cin / 8;
     constexpr int IW = kFwdTW + 2, IH = kFwdTH + 2;
     const int tx0 = blockIdx.x * kFwdTW, ty0 = blockIdx.y * kFwdTH, n = blockIdx.z;
-    for (int e = threadIdx.x; e < IH * IW * cg; e += kThreads) {
-        const int pix = e / cg, c8 = e - pix * cg;
-        const int iy = ty0 - 1 + pix / IW, ix = tx0 - 1 + pix % IW;
-        s_tile[pix * ps + c8] = __builtin_bit_cast(uint4, gather8(in, n, iy, ix, 8 * c8));
-    }
+    stage_window(s_tile, IH * IW * cg, cg, [&](int pix, int c8) {
+        return __builtin_bit_cast(uint4, gather8(in, n, ty0 - 1 + pix / IW, tx0 - 1 + pix % IW, 8 * c8));
+    });
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
     f4 acc[4][NT];
@@ -242,27 +357,7 @@ __global__ __launch_bounds__(kThreads) void conv_fwd_tiled_kernel(ConvIn in, con
     for (int m = 0; m < 4; ++m)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[m][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int kb = 0; kb < K; kb += 32) {
-        const int k = kb + 8 * g;
-        const int tap = k / cin, c0 = k - tap * cin;
-        const bool valid = tap < 9;
-        const int ky = tap / 3, kx = tap - 3 * (tap / 3);
-        bf16x8 B[NT], A[4];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int co = t * 16 + r;
-            B[t] = (co < cout && valid) ? load8(w + (int64_t)co * K + k) : zero8();
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int row = 2 * wave + (m >> 1) + ky, col = (m & 1) * 16 + r + kx;
-            A[m] = valid ? __builtin_bit_cast(bf16x8, s_tile[(row * IW + col) * ps + c0 / 8]) : zero8();
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[m][t] = mfma(A[m], B[t], acc[m][t]);
-    }
+    conv_tile_accumulate<NT, false>(s_tile, w, cin, cout, acc);
     if constexpr (STAGED) {
         // tile m holds pixels (m & 1) * 16 + 4g .. + 3 of row 2w + (m >> 1)
         int run_pix[4];
@@ -419,9 +514,11 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_kernel(const uint16_t* __
 __device__ __forceinline__ void dgrad_store_pass(const float* s_out, int c_lo, int c_hi, int ty0, int tx0, int n,
                                                  int hv, int wv, const DgradOut& o)
 {
+    // (32 channels, the usual pass: a division by a constant)
     const int groups = (c_hi - c_lo) / 4;
+    const bool full = groups == 8;
     for (int e = threadIdx.x; e < kFwdTH * kFwdTW * groups; e += kThreads) {
-        const int p = e / groups, c = c_lo + (e - p * groups) * 4;
+        const int p = full ? e / 8 : e / groups, c = c_lo + (e - p * groups) * 4;
         const int y = ty0 + p / kFwdTW, x = tx0 + p % kFwdTW;
         if (y >= hv || x >= wv) continue;
         const int64_t qq = ((int64_t)n * hv + y) * wv + x;
@@ -448,7 +545,7 @@ __device__ __forceinline__ void dgrad_store_pass(const float* s_out, int c_lo, i
             const int cc = c - o.split;
             const uint16_t* yp = o.y + qq * o.y_stride + cc;
             uint16_t* zp = o.dz + qq * o.dz_stride + cc;
-            uint16_t yv[4], out[4];
+            uint16_t yv[4];
             if (o.vec) {
                 if (o.add) {
                     const float4 b = *reinterpret_cast<const float4*>(o.add + qq * o.add_stride + cc);
@@ -470,13 +567,12 @@ __device__ __forceinline__ void dgrad_store_pass(const float* s_out, int c_lo, i
                 }
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) out[j] = f2bf(bf2f(yv[j]) > 0.0f ? v[j] : 0.0f);
+            for (int j = 0; j < 4; ++j) v[j] = bf2f(yv[j]) > 0.0f ? v[j] : 0.0f;
             if (o.vec) {
-                *reinterpret_cast<uint2*>(zp) =
-                    make_uint2((uint32_t)out[0] | (uint32_t)out[1] << 16, (uint32_t)out[2] | (uint32_t)out[3] << 16);
+                *reinterpret_cast<uint2*>(zp) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) zp[j] = out[j];
+                for (int j = 0; j < 4; ++j) zp[j] = f2bf(v[j]);
             }
         }
     }
@@ -519,17 +615,14 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_tiled_kernel(const uint16
                                                                     DgradOut o)
 {
     extern __shared__ uint4 s_tile[];
-    const int K = 9 * coutp, cg = coutp / 8, ps = cg + 1;
+    const int cg = coutp / 8;
     constexpr int IW = kFwdTW + 2, IH = kFwdTH + 2;
     const int tx0 = blockIdx.x * kFwdTW, ty0 = blockIdx.y * kFwdTH, n = blockIdx.z;
-    for (int e = threadIdx.x; e < IH * IW * cg; e += kThreads) {
-        const int pix = e / cg, c8 = e - pix * cg;
+    stage_window(s_tile, IH * IW * cg, cg, [&](int pix, int c8) {
         const int y = ty0 - 1 + pix / IW, x = tx0 - 1 + pix % IW;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if ((unsigned)y < (unsigned)ho && (unsigned)x < (unsigned)wo)
-            v = *reinterpret_cast<const uint4*>(dz + (((int64_t)n * ho + y) * wo + x) * coutp + 8 * c8);
-        s_tile[pix * ps + c8] = v;
-    }
+        if ((unsigned)y >= (unsigned)ho || (unsigned)x >= (unsigned)wo) return make_uint4(0, 0, 0, 0);
+        return *reinterpret_cast<const uint4*>(dz + (((int64_t)n * ho + y) * wo + x) * coutp + 8 * c8);
+    });
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
     f4 acc[4][NT];
@@ -537,27 +630,7 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_tiled_kernel(const uint16
     for (int m = 0; m < 4; ++m)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[m][t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int kb = 0; kb < K; kb += 32) {
-        const int k = kb + 8 * g;
-        const int tap = k / coutp, co0 = k - tap * coutp;
-        const bool valid = tap < 9;
-        const int ky = tap / 3, kx = tap - 3 * (tap / 3);
-        bf16x8 B[NT], A[4];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int c = t * 16 + r;
-            B[t] = (c < cin && valid) ? load8(wt + (int64_t)c * K + k) : zero8();
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int row = 2 * wave + (m >> 1) + 2 - ky, col = (m & 1) * 16 + r + 2 - kx;
-            A[m] = valid ? __builtin_bit_cast(bf16x8, s_tile[(row * IW + col) * ps + co0 / 8]) : zero8();
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[m][t] = mfma(A[m], B[t], acc[m][t]);
-    }
+    conv_tile_accumulate<NT, true>(s_tile, wt, coutp, cin, acc);
     if constexpr (STAGED) {
         // tile m holds pixels (m & 1) * 16 + 4g .. + 3 of row 2w + (m >> 1)
         int run_pix[4];
@@ -634,7 +707,9 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_tiled_kernel(const uint16
 // pixels, is staged in LDS once.  Chunks of 32 k (one tap, 32 output
 // channels) are added in the order of conv_dgrad_kernel, which adds only
 // zeros between them.
-template <int NT>
+// With LW the weights are staged behind the window: a wave has one to four
+// MFMAs per weight fragment, too few to cover a load from the L2 for each.
+template <int NT, bool LW>
 __global__ __launch_bounds__(kThreads) void conv_dgrad_s2_kernel(const uint16_t* __restrict__ dz, int coutp,
                                                                  int ho, int wo,
                                                                  const uint16_t* __restrict__ wt, int cin,
@@ -645,14 +720,17 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_s2_kernel(const uint16_t*
     constexpr int IW = kFwdTW / 2 + 1, IH = kFwdTH / 2 + 1;
     const int tx0 = blockIdx.x * kFwdTW, ty0 = blockIdx.y * kFwdTH, n = blockIdx.z;
     const int oy0 = ty0 / 2, ox0 = tx0 / 2;
-    for (int e = threadIdx.x; e < IH * IW * cg; e += kThreads) {
-        const int pix = e / cg, c8 = e - pix * cg;
+    stage_window(s_tile, IH * IW * cg, cg, [&](int pix, int c8) {
         const int y = oy0 + pix / IW, x = ox0 + pix % IW;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (y < ho && x < wo)
-            v = *reinterpret_cast<const uint4*>(dz + (((int64_t)n * ho + y) * wo + x) * coutp + 8 * c8);
-        s_tile[pix * ps + c8] = v;
-    }
+        if (y >= ho || x >= wo) return make_uint4(0, 0, 0, 0);
+        return *reinterpret_cast<const uint4*>(dz + (((int64_t)n * ho + y) * wo + x) * coutp + 8 * c8);
+    });
+    // [c][tap][group], a channel's row padded by one group
+    uint4* const s_w = s_tile + IH * IW * ps;
+    const int wg = 9 * cg;
+    if (LW)
+        stage_window(s_w, cin * wg, wg,
+                     [&](int c, int q) { return *reinterpret_cast<const uint4*>(wt + (int64_t)c * K + 8 * q); });
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, r = lane & 15;
     f4 acc[4][NT];
@@ -675,7 +753,12 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_s2_kernel(const uint16_t*
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const int c = t * 16 + r;
-                    const bf16x8 B = (c < cin && valid) ? load8(wt + (int64_t)c * K + tap * coutp + co0) : zero8();
+                    bf16x8 B;
+                    if (LW)   // channels past cin are not stored; the last one's weights do
+                        B = valid ? __builtin_bit_cast(bf16x8, s_w[min(c, cin - 1) * (wg + 1) + tap * cg + co0 / 8])
+                                  : zero8();
+                    else
+                        B = (c < cin && valid) ? load8(wt + (int64_t)c * K + tap * coutp + co0) : zero8();
                     acc[m][t] = mfma(A, B, acc[m][t]);
                 }
             }
@@ -957,8 +1040,9 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tiled_kernel(ConvIn in, i
                     s_in[(kx * CB + 8 * cg + ch) * SI + iy * Q + q] = v;
                 }
         }
-        // dz rows y0 .. y0 + TH - 1 (zero past the image): item (q, oy, channel group)
-        for (int e = tid; e < TH * Q * (coutp / 8); e += kThreads) {
+        // dz rows y0 .. y0 + TH - 1 (zero past the image): item (q, oy, channel
+        // group), from the last thread down: the waves the input left idle
+        for (int e = kThreads - 1 - tid; e < TH * Q * (coutp / 8); e += kThreads) {
             const int q = e % Q, oy = (e / Q) % TH, cg = e / (Q * TH);
             const int y = y0 + oy, xb = x0 + 8 * q;
             uint4 px[8];
@@ -1287,15 +1371,26 @@ vdbc_status conv_dgrad(const uint16_t* dz, int coutp, int cout, int n, int ho, i
             const size_t epi = (size_t)(cin <= 16 ? 16 : 32) * kEpiStride * 4;
             lds = lds > epi ? lds : epi;
         }
-        if (cin <= 16)
-            hipLaunchKernelGGL((conv_dgrad_s2_kernel<1>), grid, dim3(kThreads), lds, st, dz, coutp, ho, wo, wt, cin,
-                               hv, wv, out);
-        else if (cin <= 32)
-            hipLaunchKernelGGL((conv_dgrad_s2_kernel<2>), grid, dim3(kThreads), lds, st, dz, coutp, ho, wo, wt, cin,
-                               hv, wv, out);
-        else
-            hipLaunchKernelGGL((conv_dgrad_s2_kernel<4>), grid, dim3(kThreads), lds, st, dz, coutp, ho, wo, wt, cin,
-                               hv, wv, out);
+        // staged weights up to three workgroups a CU (32 x 64 channels: 37 KB)
+        const size_t win = (size_t)(kFwdTH / 2 + 1) * (kFwdTW / 2 + 1) * (coutp / 8 + 1) * 16,
+                     with_w = win + (size_t)cin * (9 * (coutp / 8) + 1) * 16;
+        const bool lw = with_w <= 53 * 1024;
+        if (lw) lds = lds > with_w ? lds : with_w;
+#define VDBC_DGRAD_S2(NTV)                                                                                            \
+    if (lw)                                                                                                           \
+        hipLaunchKernelGGL((conv_dgrad_s2_kernel<NTV, true>), grid, dim3(kThreads), lds, st, dz, coutp, ho, wo, wt, cin, \
+                           hv, wv, out);                                                                              \
+    else                                                                                                              \
+        hipLaunchKernelGGL((conv_dgrad_s2_kernel<NTV, false>), grid, dim3(kThreads), lds, st, dz, coutp, ho, wo, wt, cin, \
+                           hv, wv, out)
+        if (cin <= 16) {
+            VDBC_DGRAD_S2(1);
+        } else if (cin <= 32) {
+            VDBC_DGRAD_S2(2);
+        } else {
+            VDBC_DGRAD_S2(4);
+        }
+#undef VDBC_DGRAD_S2
         return check("conv3x3 data gradient");
     }
     if (cin <= 16)
