@@ -1,5 +1,6 @@
 // Internal helpers shared by the host-side translation units of libvdbc.
 #pragma once
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdint>
@@ -16,10 +17,13 @@ namespace vdbc {
 vdbc_status fail(vdbc_status s, const char* fmt, ...);
 void clear_error();
 
-// Runs fn(task) for task in [0, n) on `threads` workers (dynamic scheduling).
+// Runs fn(task) for task in [0, n) on `threads` workers (dynamic scheduling), on
+// fewer where they would have less than `grain` tasks each: starting a thread
+// takes some 20 us, and a machine may have hundreds.
 template <class F>
-void parallel_for(uint64_t n, unsigned threads, F&& fn)
+void parallel_for(uint64_t n, unsigned threads, F&& fn, uint64_t grain = 1)
 {
+    if (threads > n / grain) threads = (unsigned)std::max<uint64_t>(n / grain, 1);
     if (threads <= 1 || n <= 1) {
         for (uint64_t i = 0; i < n; ++i) fn(i, 0u);
         return;
