@@ -263,7 +263,9 @@ __device__ __forceinline__ void stage_window(uint4* s_tile, int n, int cg, const
 // of 32 a chunk lies in one tap: its offsets are scalar, the lanes' stay what
 // they are, and the weights are loaded up to three chunks ahead.  (Tap, channel
 // and address of every lane and chunk took some eighteen VALU instructions for
-// each MFMA.)
+// each MFMA: 64 -> 32 channels at 8 x 256^2, 61 -> 53 us with stage_window;
+// now bound by the waits of the two or three workgroups a CU holds, 21 us being
+// its bytes at the copy rate.)
 template <int NT, bool MIRROR>
 __device__ __forceinline__ void conv_tile_accumulate(const uint4* s_tile, const uint16_t* __restrict__ w, int cin,
                                                      int cout, f4 (&acc)[4][NT])
@@ -708,7 +710,8 @@ __global__ __launch_bounds__(kThreads) void conv_dgrad_tiled_kernel(const uint16
 // channels) are added in the order of conv_dgrad_kernel, which adds only
 // zeros between them.
 // With LW the weights are staged behind the window: a wave has one to four
-// MFMAs per weight fragment, too few to cover a load from the L2 for each.
+// MFMAs per weight fragment, too few to cover a load from the L2 for each (64 ->
+// 32 channels, 8 x 256^2: 67 -> 63 us; its bytes at the copy rate take 32).
 template <int NT, bool LW>
 __global__ __launch_bounds__(kThreads) void conv_dgrad_s2_kernel(const uint16_t* __restrict__ dz, int coutp,
                                                                  int ho, int wo,
@@ -1042,6 +1045,7 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tiled_kernel(ConvIn in, i
         }
         // dz rows y0 .. y0 + TH - 1 (zero past the image): item (q, oy, channel
         // group), from the last thread down: the waves the input left idle
+        // (both on the first waves: 73 us for 64 -> 32 channels at 8 x 256^2, 65 so)
         for (int e = kThreads - 1 - tid; e < TH * Q * (coutp / 8); e += kThreads) {
             const int q = e % Q, oy = (e / Q) % TH, cg = e / (Q * TH);
             const int y = y0 + oy, xb = x0 + 8 * q;

