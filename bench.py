@@ -51,7 +51,7 @@ DEFAULT_CHUNK_SPP = {"paper": 8, "sweep": 8, "mid": 4}
 # work queue in decreasing estimated tile cost (1) or in raster order (0), the
 # same autotuner's choice; the image does not depend on it
 DEFAULT_COST_ORDER = {"paper": 1, "sweep": 1, "mid": 1}
-# committed rocprofv3 counter summaries of pt_kernel<VdbAcc>, one per frame
+# committed rocprofv3 counter summaries of pt_kernel<IndexAcc>, one per frame
 PROFILES = {"paper": os.path.join(ROOT, "profiles", "pt_kernel_vdb_paper_1to10.md"),
             "mid": os.path.join(ROOT, "profiles", "pt_kernel_vdb_mid512_1to10.md")}
 PROFILE = PROFILES["paper"]
@@ -533,7 +533,7 @@ def main():
         },
         "roofline": {
             # the committed counters describe this exact workload only
-            "kernel": "pt_kernel<VdbAcc>",
+            "kernel": "pt_kernel<IndexAcc>",
             "bound": "hbm",
             "achieved": round(achieved, 2),
             "peak": HBM_PEAK_GBS,

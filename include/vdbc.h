@@ -259,10 +259,11 @@ enum {
                                       depend on it.  Ignored for dense arrays. */
     VDBC_RENDER_SPLIT = 256u,      /* PT, chunk_spp 0: the library chooses chunk_spp from the
                                       number of tiles and spp (images too small to fill the
-                                      card with whole tiles).  The workspace size then needs
-                                      the camera; in a workspace without room for the
-                                      pixel sums the tiles stay whole.  The image does not
-                                      depend on it. */
+                                      card with whole tiles), and the cost order where there
+                                      are more work items than run at once.  The workspace
+                                      size then needs the camera; in a workspace without
+                                      room for them the tiles stay whole and in raster
+                                      order.  The image does not depend on it. */
     VDBC_RENDER_COST_ORDER = 64u   /* PT: hand the tiles to the workgroups in decreasing
                                       order of an estimated cost (the majorant optical
                                       depth of four camera rays per tile) instead of in
@@ -308,7 +309,8 @@ typedef struct {
  *   then, for a path-traced launch with 0 < chunk_spp < spp (or split by
  *             VDBC_RENDER_SPLIT) only: 40 bytes per pixel of fixed-point sums
  *             (cleared and read by the render call itself)
- *   then, with VDBC_RENDER_COST_ORDER: 512 bytes and 8 per tile
+ *   then, in cost order (VDBC_RENDER_COST_ORDER, or chosen by
+ *             VDBC_RENDER_SPLIT): 512 bytes and 8 per tile
  *   then, with VDBC_RENDER_INDEX (all modes; EA and ISO have no other part
  *             but the counters): the region index, 4 bytes per entry of a
  *             grid of (ceil(nx / 8) + 2) (ceil(ny / 8) + 2) (ceil(nz / 8) + 2),
@@ -316,8 +318,8 @@ typedef struct {
  *             No index (and no bytes) past 2^30 entries, 2^24 entries per row
  *             or 2^24 rows.
  * c: the camera; needed (else VDBC_E_INVALID) only for the path tracer with
- * 0 < chunk_spp < spp, VDBC_RENDER_COST_ORDER or, where spp > 1,
- * VDBC_RENDER_SPLIT; may be NULL otherwise. */
+ * 0 < chunk_spp < spp, VDBC_RENDER_COST_ORDER or VDBC_RENDER_SPLIT; may be
+ * NULL otherwise. */
 vdbc_status vdbc_render_workspace(const vdbc_render_params* r, vdbc_dims d, const vdbc_camera* c,
                                   uint64_t* bytes);
 

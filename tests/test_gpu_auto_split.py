@@ -26,13 +26,21 @@ def test_workspace_of_the_library_split():
     base = _bytes(64, 64, 4, flags=0)[1]
     # one sample is never split; two are in a small image
     assert _bytes(64, 64, 1) == (vdbc.OK, base)
-    assert _bytes(64, 64, 1, tw=128) == (vdbc.OK, base)   # refused by the render, as without the flag
+    assert _bytes(64, 64, 1, tw=128)[0] == vdbc.E_INVALID
+    assert _bytes(64, 64, 1, tw=128, flags=0) == (vdbc.OK, base)   # refused by the render
     assert _bytes(64, 64, 2) == (vdbc.OK, base + 40 * 64 * 64)
     assert _bytes(64, 64, 2, tw=128)[0] == vdbc.E_INVALID
     assert _bytes(64, 64, 2, camera=False)[0] == vdbc.E_INVALID
-    # 6143 tiles of 32 x 8 are split, 6144 are not
-    assert _bytes(32 * 6143, 8, 4)[1] > base
-    assert _bytes(32 * 6144, 8, 4) == (vdbc.OK, base)
+    # 6143 tiles of 32 x 8 are split, 6144 are not; more than 1280 work items
+    # are queued in cost order, also where one sample leaves nothing to split
+    order = lambda tiles: -(-(512 + 8 * tiles) // 256) * 256
+    sums = lambda pixels: -(-40 * pixels // 256) * 256
+    assert _bytes(32 * 6143, 8, 4) == (vdbc.OK, base + sums(32 * 6143 * 8) + order(6143))
+    assert _bytes(32 * 6144, 8, 4) == (vdbc.OK, base + order(6144))
+    assert _bytes(32 * 1280, 8, 1) == (vdbc.OK, base)
+    assert _bytes(32 * 1281, 8, 1) == (vdbc.OK, base + order(1281))
+    assert _bytes(32 * 320, 8, 4) == (vdbc.OK, base + sums(32 * 320 * 8))
+    assert _bytes(32 * 321, 8, 4) == (vdbc.OK, base + sums(32 * 321 * 8) + order(321))
     # thin volumes past 2^24 index rows have no index
     prm = vdbc.params_c(dict(spp=1, flags=vdbc.RENDER_INDEX), vdbc.MODE_EA)
     ws = C.c_uint64(0)
@@ -42,7 +50,8 @@ def test_workspace_of_the_library_split():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("w,h,spp,dense", [(70, 33, 13, False), (33, 70, 2, True), (512, 200, 3, False)])
+@pytest.mark.parametrize("w,h,spp,dense", [(70, 33, 13, False), (33, 70, 2, True), (512, 200, 3, False), (520, 470, 4, False),
+                                            (1300, 512, 1, False)])
 def test_split_by_the_library_is_bit_identical(w, h, spp, dense):
     _build.ensure_built()
     v = synth.mid_volume(n=64)
@@ -55,10 +64,10 @@ def test_split_by_the_library_is_bit_identical(w, h, spp, dense):
     r.ws.fill_(0xA5)
     a = r.launch().clone(), r.aov.clone()
     whole = vdbc.Renderer(field, cam, med, dict(prm, chunk_spp=spp), vdbc.MODE_PT, aov=True, background=bg)
-    assert not whole.prm.flags & vdbc.RENDER_SPLIT and whole.ws_bytes < r.ws_bytes
+    assert not whole.prm.flags & vdbc.RENDER_SPLIT and whole.ws_bytes <= r.ws_bytes
     b = whole.launch().clone(), whole.aov.clone()
     assert all(torch.equal(x.view(torch.int32), y.view(torch.int32)) for x, y in zip(a, b))
-    # no room for the sums: whole tiles
+    # no room for the sums and the order: whole tiles
     r.ws_bytes = whole.ws_bytes
     r.image.zero_()
     assert torch.equal(r.launch().view(torch.int32), b[0].view(torch.int32))
