@@ -57,3 +57,18 @@ def test_bf16_outputs_round_to_nearest_even():
     want = (bias + 0.0).to(torch.bfloat16).expand(1, 8, 32, 16)
     ok = (got.view(torch.int16) == want.contiguous().view(torch.int16)) | (got.isnan() & want.isnan())
     assert bool(ok.all()), (got[0, 0, 0], want[0, 0, 0])
+
+
+@pytest.mark.parametrize("h,w", [(730, 722), (1030, 1026)])
+def test_stride_two_forward_of_large_images(h, w):
+    # more pixel tiles a wave from 131,072 and 262,144 output pixels on: the
+    # rows are those of a strip of the image, bit for bit
+    gen = torch.Generator(device="cuda").manual_seed(h)
+    a = torch.randn((1, h, w, 32), generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn((64, 3, 3, 32), generator=gen, device="cuda").to(torch.bfloat16)
+    bias = torch.randn(64, generator=gen, device="cuda")
+    out = vdbc.conv3x3(a, None, 0, 2, k, bias, 64, relu=True)
+    for y in (0, (h // 2) & ~1, (h - 48) & ~1):
+        strip = vdbc.conv3x3(a[:, y:y + 48].contiguous(), None, 0, 2, k, bias, 64, relu=True)
+        lo = 0 if y == 0 else 1
+        assert torch.equal(out[:, y // 2 + lo:y // 2 + 23], strip[:, lo:23])
