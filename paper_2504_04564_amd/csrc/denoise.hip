@@ -979,7 +979,7 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_kernel(ConvIn in, int str
 constexpr int kWgTW = 32;
 
 template <int MT, int CB, int TH, int S>
-__global__ __launch_bounds__(kThreads) void conv_wgrad_tiled_kernel(ConvIn in, int ho, int wo,
+__global__ __launch_bounds__(kThreads, 2) void conv_wgrad_tiled_kernel(ConvIn in, int ho, int wo,
                                                                     const uint16_t* __restrict__ dz, int coutp,
                                                                     int rows, int bands,
                                                                     float* __restrict__ partial,
@@ -1021,16 +1021,54 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tiled_kernel(ConvIn in, i
         const uint32_t w = ch < 2 ? v.x : ch < 4 ? v.y : ch < 6 ? v.z : v.w;
         return (ch & 1) ? w >> 16 : w & 0xFFFFu;
     };
+    // A step's loads, one item a thread, issued before the MFMAs of the step
+    // before (two waves a SIMD leave the registers to hold them): threads from 0
+    // on take input items (8 output columns of input row S * y0 - 1 + row, 8
+    // channels), those at the end dz items (8 columns of dz row y0 + row), so
+    // that all waves stage.  Both are NP pixels of a row at the
+    // same eight channels; pixels outside are read inside and cleared when
+    // they are stored, so that the loads have no branches between them (with
+    // branches, and issued ahead, 79 us for 64 -> 32 channels at 8 x 256^2; not
+    // ahead and all items on the first waves, 73; 59 so).  Bound by the steps'
+    // waits: two workgroups a CU, as more of them write more partials.
+    constexpr int NI = IH * Q * (CB / 8), ND = TH * Q * MT * 2;
+    static_assert(NI + ND <= kThreads, "one staging item per thread");
+    const bool is_in = tid < NI, is_dz = tid >= kThreads - ND && tid - (kThreads - ND) < TH * Q * (coutp / 8);
+    const int et = is_in ? tid : is_dz ? tid - (kThreads - ND) : 0, q = et % Q;
+    const int row = is_in ? (et / Q) % IH : (et / Q) % TH, cg = is_in ? et / (Q * IH) : et / (Q * TH);
+    const int hv = in.up ? 2 * in.hs : in.hs, wv = in.up ? 2 * in.ws : in.ws;
+    const int c8 = is_in ? cb0 + 8 * cg : 8 * cg;
+    const bool in_b = is_in && c8 >= in.ca && c8 < cin, any = is_dz || (is_in && c8 < cin);
+    const int cc = any ? (in_b ? c8 - in.ca : c8) : 0;
+    const uint16_t* const src = (is_in ? (in_b ? in.b : in.a) : dz) + cc;
+    const int pitch = is_in ? (in_b ? in.cb : in.ca) : coutp, up = is_in ? in.up : 0;
+    const int src_h = is_in ? in.hs : ho, src_w = is_in ? in.ws : wo;
+    const int x_first = is_in ? S * (x0 + 8 * q) - 1 : x0 + 8 * q, x_end = is_in ? wv : wo;
+    uint32_t x_in = 0;   // bit m: pixel x_first + m lies inside
+#pragma unroll
+    for (int m = 0; m < NP; ++m) x_in |= (unsigned)(x_first + m) < (unsigned)x_end ? 1u << m : 0u;
+    uint4 px[NP] = {};
+    uint32_t px_in = 0;
+    auto fetch = [&](int y0) {
+        if (!any) return;   // channels past cin stay zero
+        const int y = is_in ? S * y0 - 1 + row : y0 + row, y_lim = is_in ? hv : y_end;
+        px_in = (unsigned)y < (unsigned)y_lim ? x_in : 0u;
+        const int yc = min(max(y, 0), y_lim - 1) >> up;
+        const uint16_t* const line = src + ((int64_t)n * src_h + yc) * src_w * pitch;
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const int x = min(max(x_first + m, 0), x_end - 1) >> up;
+            px[m] = *reinterpret_cast<const uint4*>(line + (int64_t)x * pitch);
+        }
+    };
+    fetch(band * rows);
     for (int y0 = band * rows; y0 < y_end; y0 += TH) {
-        // input rows S * y0 - 1 .. : item (q, iy, channel group), so that
-        // neighbouring threads write neighbouring 16-byte units
-        for (int e = tid; e < IH * Q * (CB / 8); e += kThreads) {
-            const int q = e % Q, iy = (e / Q) % IH, cg = e / (Q * IH);
-            const int c8 = cb0 + 8 * cg, y = S * y0 - 1 + iy, xb = S * (x0 + 8 * q) - 1;
-            uint4 px[NP];
+        if (px_in != (1u << NP) - 1u) {
 #pragma unroll
             for (int m = 0; m < NP; ++m)
-                px[m] = c8 < cin ? __builtin_bit_cast(uint4, gather8(in, n, y, xb + m, c8)) : make_uint4(0, 0, 0, 0);
+                if (!((px_in >> m) & 1u)) px[m] = make_uint4(0, 0, 0, 0);
+        }
+        if (is_in) {
 #pragma unroll
             for (int kx = 0; kx < 3; ++kx)
 #pragma unroll
@@ -1040,21 +1078,9 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tiled_kernel(ConvIn in, i
                     v.y = half(px[2 * S + kx], ch) | half(px[3 * S + kx], ch) << 16;
                     v.z = half(px[4 * S + kx], ch) | half(px[5 * S + kx], ch) << 16;
                     v.w = half(px[6 * S + kx], ch) | half(px[7 * S + kx], ch) << 16;
-                    s_in[(kx * CB + 8 * cg + ch) * SI + iy * Q + q] = v;
+                    s_in[(kx * CB + 8 * cg + ch) * SI + row * Q + q] = v;
                 }
-        }
-        // dz rows y0 .. y0 + TH - 1 (zero past the image): item (q, oy, channel
-        // group), from the last thread down: the waves the input left idle
-        // (both on the first waves: 73 us for 64 -> 32 channels at 8 x 256^2, 65 so)
-        for (int e = kThreads - 1 - tid; e < TH * Q * (coutp / 8); e += kThreads) {
-            const int q = e % Q, oy = (e / Q) % TH, cg = e / (Q * TH);
-            const int y = y0 + oy, xb = x0 + 8 * q;
-            uint4 px[8];
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-                px[m] = (y < y_end && xb + m < wo)
-                            ? *reinterpret_cast<const uint4*>(dz + (((int64_t)n * ho + y) * wo + xb + m) * coutp + 8 * cg)
-                            : make_uint4(0, 0, 0, 0);
+        } else if (is_dz) {
 #pragma unroll
             for (int ch = 0; ch < 8; ++ch) {
                 uint4 v;
@@ -1062,10 +1088,11 @@ __global__ __launch_bounds__(kThreads) void conv_wgrad_tiled_kernel(ConvIn in, i
                 v.y = half(px[2], ch) | half(px[3], ch) << 16;
                 v.z = half(px[4], ch) | half(px[5], ch) << 16;
                 v.w = half(px[6], ch) | half(px[7], ch) << 16;
-                s_dz[(8 * cg + ch) * SD + oy * Q + q] = v;
+                s_dz[(8 * cg + ch) * SD + row * Q + q] = v;
             }
         }
         __syncthreads();
+        if (y0 + TH < y_end) fetch(y0 + TH);
         if (bias && tid < coutp) {
 #pragma unroll
             for (int e = 0; e < TH * Q; ++e) {
