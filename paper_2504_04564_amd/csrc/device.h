@@ -40,40 +40,6 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& c0, uint32_t& c1, uint32
     }
 }
 
-// One random stream of a path: key (seed_lo ^ pixel, seed_hi), counter
-// (block, sample, stream << 16 | bounce, frame); draw d is word d & 3 of
-// block d >> 2; u = (x >> 8) * 2^-24.
-struct Rng {
-    uint32_t k0, k1, sample, tag, frame;
-    uint32_t d;
-    uint32_t w0, w1, w2, w3;
-
-    __device__ void init(uint32_t key0, uint32_t key1, uint32_t s, uint32_t bounce,
-                         uint32_t stream, uint32_t f)
-    {
-        k0 = key0;
-        k1 = key1;
-        sample = s;
-        tag = (stream << 16) | bounce;
-        frame = f;
-        d = 0;
-    }
-    __device__ __forceinline__ float next()
-    {
-        const uint32_t q = d & 3u;
-        if (q == 0) {
-            w0 = d >> 2;
-            w1 = sample;
-            w2 = tag;
-            w3 = frame;
-            philox4x32_10(w0, w1, w2, w3, k0, k1);
-        }
-        ++d;
-        const uint32_t x = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
-        return (float)(x >> 8) * (1.0f / 16777216.0f);
-    }
-};
-
 // ---------------------------------------------------------------- fields
 
 // Where the 512 values of a leaf-sized region live: value(n3) = p[n3 & m].
@@ -125,7 +91,6 @@ enum CachePolicy { kCacheNone = 0, kCacheLeaf = 1, kCacheLeafLower = 2 };
 // lower node and the last leaf, reused across consecutive samples of one thread.
 template <int CP>
 struct VdbAccT {
-    static constexpr bool kTree = true;   // regions resolvable leaf by leaf
     VdbView v;
     int clx, cly, clz;       // cached leaf coordinates (voxel >> 3)
     LeafH cleaf;
@@ -298,7 +263,6 @@ struct IndexView {
 // wave, once per leaf of the footprint.
 template <bool WIDE>
 struct IndexAccT {
-    static constexpr bool kTree = false;
     IndexView v;
     __device__ void reset() {}
     __device__ __forceinline__ float background() const { return v.background; }
@@ -354,7 +318,6 @@ struct DenseView {
 // The "3D texture" baseline: a plain x-fastest float32 array read in
 // software, background outside the volume.
 struct DenseAcc {
-    static constexpr bool kTree = false;
     DenseView v;
     __device__ void reset() {}
     __device__ __forceinline__ float background() const { return v.background; }

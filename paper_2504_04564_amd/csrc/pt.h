@@ -66,9 +66,10 @@ __global__ __launch_bounds__(kBlock) void coarse_bits_kernel(const float* __rest
     coarse_bits_block(maj, g, bits, blockIdx.x);
 }
 
-// Random words of a lane's path segment (the stream layout of Rng in
-// device.h), generated ahead of their use: a ring of two Philox blocks per
-// lane in LDS, filled at one place of the path loop.  Philox at every draw
+// Random words of a lane's path segment: key (seed_lo ^ pixel, seed_hi),
+// counter (block, sample, stream << 16 | bounce, frame); draw d is word d & 3 of
+// block d >> 2, u = (x >> 8) * 2^-24.  Generated ahead of their use: a ring of
+// two Philox blocks per lane in LDS, filled at one place of the path loop.  Philox at every draw
 // site ran for a handful of lanes each time (11 % lane utilisation in the free
 // flights, a third of the kernel's VALU instructions).
 struct Stream {
