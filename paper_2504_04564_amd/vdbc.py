@@ -352,7 +352,8 @@ def params_c(p: dict, mode: int) -> RenderParamsC:
     """vdbc_render_params from a dict: spp (1), max_bounces (8), macrocell
     (8), flags (0; RENDER_*), step (0.5), t_terminate (0), seed (0), frame
     (0), tile_w (8: pixels per wave row), iso (0.5), refine (12), chunk_spp
-    (0: one work item per tile; else samples per work item)."""
+    (samples per work item; 0: one work item per tile, or with RENDER_SPLIT,
+    which Renderer sets then, the library's choice)."""
     r = RenderParamsC()
     r.mode = mode
     r.spp = p.get("spp", 1)
@@ -391,7 +392,7 @@ class Renderer:
         # accessor cache policy is asked for
         if not self.dense and not self.prm.flags & (RENDER_CACHE_NONE | RENDER_CACHE_LEAF):
             self.prm.flags |= RENDER_INDEX
-        if mode == MODE_PT and self.prm.chunk_spp == 0:   # the library's choice of samples per work item
+        if mode == MODE_PT and self.prm.chunk_spp == 0:   # the library's choice of work items
             self.prm.flags |= RENDER_SPLIT
         ws = C.c_uint64(0)
         _check(load().vdbc_render_workspace(C.byref(self.prm), self.dims, C.byref(self.cam), C.byref(ws)))
