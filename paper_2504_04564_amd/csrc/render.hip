@@ -413,7 +413,7 @@ __device__ __forceinline__ MarchRay march_ray(const View& v, const CameraK& cam)
 // The first lattice index past the empty block of level L (2^(L - 1) entries
 // a side) that holds sample k in entry e; at least k + 1.  Every sample
 // before it reads the background (kHddaEps: far beyond the rounding of the
-// exit and of a sample's position).
+// exit and of a sample's position, from as near as skip_is_exact() asks for).
 __device__ __forceinline__ int march_skip(const MarchRay& r, int L, const int e[3], int k, float inv_step)
 {
     const int keep = -(1 << (L - 1)), size = 8 << (L - 1);
@@ -1038,9 +1038,10 @@ static int device_cus()
     return cus;
 }
 
-// Whether the marchers may skip empty blocks where the caller did not ask for
-// it: the image stays the same bit for bit while a sample's position is
-// rounded by far less than kHddaEps, i.e. while the camera is near.
+// Whether the marchers may skip empty blocks, asked to or not: the image stays
+// the same bit for bit while a sample's position is rounded by far less than
+// kHddaEps, i.e. while the camera is near.  (From 300,000 voxels away 0.6 % of the
+// skips would pass over a sample that reads more than the background.)
 static bool skip_is_exact(const CameraK& c, const VdbView& v)
 {
     double far = (double)v.nx + v.ny + v.nz;
@@ -1108,7 +1109,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
             } else {
             if (ix.on && !count) {
                 if ((s = launch_index(v, ix, st))) return s;
-                const bool skip = hdda || skip_is_exact(cam, v);
+                const bool skip = skip_is_exact(cam, v);
                 if (ix.wide && skip) ISO_QUAD(IndexAccT<true>, IndexView, ix.v, true);
                 else if (ix.wide) ISO_QUAD(IndexAccT<true>, IndexView, ix.v, false);
                 else if (skip) ISO_QUAD(IndexAccT<false>, IndexView, ix.v, true);
@@ -1156,7 +1157,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
             } else {
             if (ix.on && !count) {
                 if ((s = launch_index(v, ix, st))) return s;
-                const bool skip = clear && (hdda || skip_is_exact(cam, v));
+                const bool skip = clear && skip_is_exact(cam, v);
                 if (ix.wide && skip) EA_QUAD(IndexAccT<true>, IndexView, ix.v, true);
                 else if (ix.wide) EA_QUAD(IndexAccT<true>, IndexView, ix.v, false);
                 else if (skip) EA_QUAD(IndexAccT<false>, IndexView, ix.v, true);
