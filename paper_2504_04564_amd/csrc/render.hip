@@ -1144,6 +1144,9 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
                 return fail(VDBC_E_INVALID, "EA step too small for this volume (> 2^24 samples per ray)");
             const bool clear = host_alpha(m, v.background) == 0.0f;
             const bool hdda = (r->flags & VDBC_RENDER_HDDA) && clear;
+            // past 1 a ray ends at the first sample it takes: which one that is
+            // stays with the kernel of one thread per ray and its own skips
+            const bool first_only = r->t_terminate > 1.0f;
 #define EA_QUAD(ACC, VIEW, FIELD, SKIP)                                                                          \
     hipLaunchKernelGGL((ea_quad_kernel<ACC, VIEW, SKIP>), quads, dim3(kBlock), 0, st, FIELD, cam, m, r->step, \
                        1.0f / r->step, r->t_terminate, image)
@@ -1155,7 +1158,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
                     EA_QUAD(DenseAcc, DenseView, v, false);
                 return launch_check("ea render");
             } else {
-            if (ix.on && !count) {
+            if (ix.on && !count && !first_only) {
                 if ((s = launch_index(v, ix, st))) return s;
                 const bool skip = clear && skip_is_exact(cam, v);
                 if (ix.wide && skip) EA_QUAD(IndexAccT<true>, IndexView, ix.v, true);

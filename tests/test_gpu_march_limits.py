@@ -1,6 +1,7 @@
 """Calls at the limits of the marchers with four lanes per ray, against the
 kernels with one thread per ray (counting launches): cameras so far away that a
-position's rounding passes the skips' margin."""
+position's rounding passes the skips' margin, and a termination threshold that
+ends a ray at its first sample."""
 import math
 
 import numpy as np
@@ -39,3 +40,17 @@ def test_skipping_is_exact_from_far_away(voxels):
             for flags in (0, vdbc.RENDER_HDDA):
                 r = vdbc.Renderer(g, cam, med, dict(step=0.5, iso=0.3, flags=flags), mode)
                 assert np.array_equal(_bits(r.launch()), want), (az, mode, flags)
+
+
+@pytest.mark.parametrize("flags", [0, vdbc.RENDER_HDDA])
+@pytest.mark.parametrize("t_end", [1.0, 1.5])
+@pytest.mark.parametrize("dense", [False, True])
+def test_termination_at_the_first_sample(dense, t_end, flags):
+    vol = synth.cloud_volume((61, 72, 90), seed=4)
+    dims = tuple(reversed(vol.shape))
+    field, bg = (torch.from_numpy(vol).cuda(), 0.0) if dense else (vdbc.Grid(vdbc.encode(vol, 0.15)[0]), None)
+    cam, med = scenes.orbit_camera(dims, 70, 50), scenes.ea_medium(8.0)
+    prm = dict(step=0.5, t_terminate=t_end, flags=flags)
+    r = vdbc.Renderer(field, cam, med, prm, vdbc.MODE_EA, background=bg)
+    every = vdbc.Renderer(field, cam, med, dict(prm, flags=flags | vdbc.RENDER_COUNT), vdbc.MODE_EA, background=bg)
+    assert np.array_equal(_bits(r.launch()), _bits(every.launch()))
