@@ -400,7 +400,8 @@ __device__ __forceinline__ MarchRay march_ray(const View& v, const CameraK& cam)
 {
     MarchRay r;
     const int q = (threadIdx.x & 63) >> 2, w = threadIdx.x >> 6;
-    const uint32_t across = (uint32_t)(cam.width + 7) / 8u, by = blockIdx.x / across, bx = blockIdx.x - by * across;
+    const uint32_t blk = blockIdx.y * gridDim.x + blockIdx.x;   // past the image: no ray is live
+    const uint32_t across = (uint32_t)(cam.width + 7) / 8u, by = blk / across, bx = blk - by * across;
     r.px = (int)bx * 8 + (w & 1) * 4 + (q & 3);
     r.py = (int)by * 8 + (w >> 1) * 4 + (q >> 2);
     r.live = r.px < cam.width && r.py < cam.height;
@@ -1081,7 +1082,10 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     if (ws && reinterpret_cast<uintptr_t>(ws) % 256)
         return fail(VDBC_E_INVALID, "workspace must be 256-byte aligned");
     dim3 grid((cam.width + kTile - 1) / kTile, (cam.height + kTile - 1) / kTile);
-    const dim3 quads((unsigned)((cam.width + 7) / 8) * (unsigned)((cam.height + 7) / 8));
+    // workgroups of 8 x 8 pixels; a launch takes less than 2^32 threads along x
+    // (images of 2^30 pixels have more) and 65535 workgroups along y
+    const unsigned quad_groups = (unsigned)((cam.width + 7) / 8) * (unsigned)((cam.height + 7) / 8), quad_x = 1u << 23;
+    const dim3 quads(std::min(quad_groups, quad_x), (quad_groups + quad_x - 1) / quad_x);
     if constexpr (MARCH) {
         if (r->mode == VDBC_MODE_ISO) {
             if (!(r->step > 0.0f) || !std::isfinite(r->step))

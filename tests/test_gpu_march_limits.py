@@ -1,7 +1,8 @@
 """Calls at the limits of the marchers with four lanes per ray, against the
 kernels with one thread per ray (counting launches): cameras so far away that a
-position's rounding passes the skips' margin, and a termination threshold that
-ends a ray at its first sample."""
+position's rounding passes the skips' margin, a termination threshold that
+ends a ray at its first sample, and images with more lanes than one grid
+dimension takes."""
 import math
 
 import numpy as np
@@ -54,3 +55,26 @@ def test_termination_at_the_first_sample(dense, t_end, flags):
     r = vdbc.Renderer(field, cam, med, prm, vdbc.MODE_EA, background=bg)
     every = vdbc.Renderer(field, cam, med, dict(prm, flags=flags | vdbc.RENDER_COUNT), vdbc.MODE_EA, background=bg)
     assert np.array_equal(_bits(r.launch()), _bits(every.launch()))
+
+
+def test_images_past_two_to_the_thirty_pixels():
+    # 4 lanes a pixel: 2^32 + 2^20 threads
+    w, h = 32768, 32776
+    vol = np.random.default_rng(2).random((3, 16, 16), dtype=np.float32)
+    g = vdbc.Grid(vdbc.encode(vol, 1.0, flags=vdbc.BG_EXPLICIT)[0])
+    cam = dict(kind=0, width=w, height=h, lower_left=(-1.0, -1.0, -1.0), du=(18.0 / w, 0.0, 0.0),
+               dv=(0.0, 18.0 / h, 0.0), dir=(0.0, 0.0, 1.0))
+    dense = torch.from_numpy(vol).cuda()
+    for field, mode, bg in ((g, vdbc.MODE_EA, None), (dense, vdbc.MODE_ISO, 0.0)):
+        med, prm = scenes.ea_medium(8.0), dict(step=1.0, iso=0.5, refine=1)
+        r = vdbc.Renderer(field, cam, med, prm, mode, background=bg)
+        every = vdbc.Renderer(field, cam, med, dict(prm, flags=vdbc.RENDER_COUNT), mode, background=bg)
+        r.image.fill_(-1.0)
+        r.launch()
+        every.launch()
+        assert float(r.image[-2000, w // 2, 3]) >= 0.0
+        for y in range(0, h, 4096):
+            a, b = r.image[y:y + 4096], every.image[y:y + 4096]
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32)), y
+        del r, every
+        torch.cuda.empty_cache()
