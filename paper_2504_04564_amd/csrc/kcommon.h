@@ -58,6 +58,10 @@ __device__ __forceinline__ void block_count(uint32_t n, unsigned long long* coun
     if (threadIdx.x == 0 && s) atomicAdd(counter, (unsigned long long)s);
 }
 
+// Workgroup of a launch over wide_grid(): those past the number asked for have
+// nothing to do.
+__device__ __forceinline__ uint32_t wide_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Orders the LDS of one wave, written and read by its own lanes only.
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -66,6 +70,15 @@ __device__ __forceinline__ void wave_lds_fence()
 }
 
 // ---------------------------------------------------------------- host helpers
+
+// At least `groups` (below 2^31) workgroups of kBlock threads: a launch takes
+// less than 2^32 threads along x, and with more comes back without an error and
+// without some of them.
+static inline dim3 wide_grid(uint64_t groups)
+{
+    constexpr uint64_t x = 1u << 23;
+    return dim3((unsigned)std::min(groups, x), (unsigned)((groups + x - 1) / x));
+}
 
 static inline vdbc_status launch_check(const char* what)
 {

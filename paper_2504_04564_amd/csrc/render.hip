@@ -180,7 +180,7 @@ __device__ __forceinline__ void majorant_tree_group(const VdbView& view, const M
     if (C <= kMajorantWaveCell) {
         const uint32_t cell = blk * (kBlock / 64) + (threadIdx.x >> 6);
         if (cell < (uint32_t)gx * (uint32_t)gy * (uint32_t)gz) majorant_tree<true>(view, m, C, gx, gy, cell, out, sh);
-    } else {
+    } else if (blk < (uint32_t)gx * (uint32_t)gy * (uint32_t)gz) {
         majorant_tree<false>(view, m, C, gx, gy, blk, out, sh);
     }
 }
@@ -193,7 +193,7 @@ static uint64_t majorant_groups(int C, uint64_t cells)
 __global__ __launch_bounds__(kBlock) void majorant_tree_kernel(VdbView view, MediumK m, int C, int gx, int gy, int gz,
                                                                float* __restrict__ out)
 {
-    majorant_tree_group(view, m, C, gx, gy, gz, blockIdx.x, out);
+    majorant_tree_group(view, m, C, gx, gy, gz, wide_block(), out);
 }
 
 // Dense array.  A workgroup takes a run of macrocells along x, 256 voxels at
@@ -203,15 +203,17 @@ __global__ __launch_bounds__(kBlock) void majorant_tree_kernel(VdbView view, Med
 // by the array's bytes, (C+2)^2 / C^2 times.  (A thread per row of a cell's own
 // footprint read 72-byte rows, column by column: 364 us at 512^3 with cells of
 // 16; 129 us so, where the array at the copy rate takes 113.)
-__global__ __launch_bounds__(kBlock) void majorant_dense_kernel(DenseView view, MediumK m, int C, int gx, int gy,
+__global__ __launch_bounds__(kBlock) void majorant_dense_kernel(DenseView view, MediumK m, int C, int gx, int gy, int gz,
                                                                 int run, int runs, float* __restrict__ out)
 {
     __shared__ float col[2][kBlock + 2][4];   // min, max of the run's columns, from the one before it; by row set
     __shared__ float ends[2][2][kBlock / 64];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int width = run * C, chunks = (width + 63) / 64, sets = chunks == 1 ? 4 : chunks == 2 ? 2 : 1;
-    const int rx = (int)(blockIdx.x % (unsigned)runs), cy = (int)((blockIdx.x / (unsigned)runs) % (unsigned)gy),
-              cz = (int)(blockIdx.x / ((unsigned)runs * (unsigned)gy));
+    const uint32_t blk = wide_block();
+    const int rx = (int)(blk % (unsigned)runs), cy = (int)((blk / (unsigned)runs) % (unsigned)gy),
+              cz = (int)(blk / ((unsigned)runs * (unsigned)gy));
+    if (cz >= gz) return;   // the whole workgroup
     const int E = C + 2, x0 = rx * width, y0 = C * cy - 1, z0 = C * cz - 1;
     const int64_t sy = view.nx, sz = (int64_t)view.nx * view.ny;
     const float B = view.background;
@@ -400,7 +402,7 @@ __device__ __forceinline__ MarchRay march_ray(const View& v, const CameraK& cam)
 {
     MarchRay r;
     const int q = (threadIdx.x & 63) >> 2, w = threadIdx.x >> 6;
-    const uint32_t blk = blockIdx.y * gridDim.x + blockIdx.x;   // past the image: no ray is live
+    const uint32_t blk = wide_block();   // past the image: no ray is live
     const uint32_t across = (uint32_t)(cam.width + 7) / 8u, by = blk / across, bx = blk - by * across;
     r.px = (int)bx * 8 + (w & 1) * 4 + (q & 3);
     r.py = (int)by * 8 + (w >> 1) * 4 + (q >> 2);
@@ -1003,7 +1005,7 @@ static vdbc_status launch_majorant(const VdbView& v, const MediumK& m, uint32_t 
     uint64_t cells;
     vdbc_status s = majorant_cells(v.nx, v.ny, v.nz, C, g, &cells);
     if (s) return s;
-    hipLaunchKernelGGL(majorant_tree_kernel, dim3((unsigned)majorant_groups((int)C, cells)), dim3(kBlock), 0, st, v, m,
+    hipLaunchKernelGGL(majorant_tree_kernel, wide_grid(majorant_groups((int)C, cells)), dim3(kBlock), 0, st, v, m,
                        (int)C, g[0], g[1], g[2], out);
     return launch_check("majorant");
 }
@@ -1016,8 +1018,8 @@ static vdbc_status launch_majorant(const DenseView& v, const MediumK& m, uint32_
     if (s) return s;
     // 64, 128 or 256 voxels of cells: narrow volumes leave no wave idle
     const int width = v.nx <= 64 ? 64 : v.nx <= 128 ? 128 : 256, run = width / (int)C, runs = (g[0] + run - 1) / run;
-    hipLaunchKernelGGL(majorant_dense_kernel, dim3((unsigned)runs * (unsigned)g[1] * (unsigned)g[2]), dim3(kBlock), 0, st,
-                       v, m, (int)C, g[0], g[1], run, runs, out);
+    hipLaunchKernelGGL(majorant_dense_kernel, wide_grid((uint64_t)runs * g[1] * g[2]), dim3(kBlock), 0, st, v, m, (int)C, g[0],
+                       g[1], g[2], run, runs, out);
     return launch_check("majorant");
 }
 
@@ -1082,10 +1084,7 @@ static vdbc_status render_impl(const View& v, const vdbc_camera* c, const vdbc_m
     if (ws && reinterpret_cast<uintptr_t>(ws) % 256)
         return fail(VDBC_E_INVALID, "workspace must be 256-byte aligned");
     dim3 grid((cam.width + kTile - 1) / kTile, (cam.height + kTile - 1) / kTile);
-    // workgroups of 8 x 8 pixels; a launch takes less than 2^32 threads along x
-    // (images of 2^30 pixels have more) and 65535 workgroups along y
-    const unsigned quad_groups = (unsigned)((cam.width + 7) / 8) * (unsigned)((cam.height + 7) / 8), quad_x = 1u << 23;
-    const dim3 quads(std::min(quad_groups, quad_x), (quad_groups + quad_x - 1) / quad_x);
+    const dim3 quads = wide_grid((uint64_t)((cam.width + 7) / 8) * (uint64_t)((cam.height + 7) / 8));   // 8 x 8 pixels
     if constexpr (MARCH) {
         if (r->mode == VDBC_MODE_ISO) {
             if (!(r->step > 0.0f) || !std::isfinite(r->step))
