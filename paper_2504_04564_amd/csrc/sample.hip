@@ -25,18 +25,28 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(View view, const float* 
 // the code of all eight corners, the last seven for an eighth of its lanes.
 // Here every lane descends for its lower corner, then the wave's further
 // regions (some 27 for 64 random positions) are listed in LDS and the lanes
-// take one descent each, whoever's it is.  The two corners of a row come in one
-// 8-byte load.  16.8 million positions in a 512^3 tree at 1:10: 403 -> 289 us
-// (34 -> 19 vector loads and 528 -> 407 VALU instructions a wave); the address
-// units of the caches are busy for 76 % of it, the vector units for 64 %.
+// take one descent each, whoever's it is, from the lower node that its owner
+// found.  The two corners of a row come in one 8-byte load.  16.8 million
+// positions in a 512^3 tree at 1:10: 403 -> 282 us, the address units of the
+// caches busy for three quarters of it, the vector units for two thirds.
+// Ordered positions are bound by VALU issue, and a wave without a crossing, or
+// with 64 lanes in a few leaves, must not pay for the sharing: the first reads
+// its one region, the second descends once a leaf and region.  Positions past
+// the volume cross nothing.  With one descent a lane and region, with the sharing
+// alone, and so: a lattice of 512 x 512 x 32 102, 106 and 93 us, 4.2 million
+// positions on a line 30.3, 35.6 and 31.7, nearly all outside 30.7, 39.2 and 22.
 struct SampleWave {
-    uint64_t region[8][64];   // by crossed axes: where its values are | 1 (a stored leaf)
+    uint64_t region[7][64];   // by crossed axes - 1: where its values are | 1 (a stored leaf)
     uint16_t item[7 * 64];    // lane | crossed axes << 6
 };
 
-__device__ __forceinline__ uint64_t region_word(const LeafH& h) { return reinterpret_cast<uint64_t>(h.p) | (h.m & 1u); }
 // (A pointer made from an integer would be read by flat loads.)
 typedef const __attribute__((address_space(1))) float GlobalFloat;
+typedef const __attribute__((address_space(1))) Word GlobalWord;
+typedef float f32x2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef const __attribute__((address_space(1))) f32x2 GlobalPair;
+
+__device__ __forceinline__ uint64_t region_word(const LeafH& h) { return reinterpret_cast<uint64_t>(h.p) | (h.m & 1u); }
 __device__ __forceinline__ GlobalFloat* region_values(uint64_t r) { return reinterpret_cast<GlobalFloat*>(r & ~1ull); }
 
 __global__ __launch_bounds__(kBlock) void sample_tree_kernel(VdbView view, const float* __restrict__ pos, uint64_t n,
@@ -51,58 +61,109 @@ __global__ __launch_bounds__(kBlock) void sample_tree_kernel(VdbView view, const
     const float pz = __builtin_amdgcn_fmed3f(pos[3 * at + 2], -2.0f, (float)view.nz + 1.0f);
     const float fx0 = floorf(px), fy0 = floorf(py), fz0 = floorf(pz);
     const int i = (int)fx0, j = (int)fy0, k = (int)fz0;
-    const int lx = i >> 3, ly = j >> 3, lz = k >> 3;
-    const bool sx = (i & 7) == 7;
-    const uint32_t cross = (sx ? 1u : 0u) | ((j & 7) == 7 ? 2u : 0u) | ((k & 7) == 7 ? 4u : 0u);
-    VdbAccT<kCacheNone> acc{view};
+    // no corner inside the volume: the background for all, without a descent
+    const bool none = (unsigned)(i + 1) > (unsigned)view.nx || (unsigned)(j + 1) > (unsigned)view.ny ||
+                      (unsigned)(k + 1) > (unsigned)view.nz;
+    const int lx = none ? -1 : i >> 3, ly = j >> 3, lz = k >> 3;
+    const bool sx = !none && (i & 7) == 7;
+    const uint32_t cross = none ? 0u : (sx ? 1u : 0u) | ((j & 7) == 7 ? 2u : 0u) | ((k & 7) == 7 ? 4u : 0u);
+    VdbAcc acc{view};
     acc.reset();
     const uint64_t own = region_word(acc.resolve(lx, ly, lz));
-    sw.region[0][lane] = own;
-    // 1, 3 or 7 further regions: the non-empty subsets of the crossed axes
-    const uint64_t m1 = __ballot(cross != 0u), m2 = __ballot((cross & (cross - 1u)) != 0u), m4 = __ballot(cross == 7u);
-    const uint32_t total = (uint32_t)(__popcll(m1) + 2 * __popcll(m2) + 4 * __popcll(m4));
-    const uint64_t lower = (1ull << lane) - 1u;
-    uint32_t o = (uint32_t)(__popcll(m1 & lower) + 2 * __popcll(m2 & lower) + 4 * __popcll(m4 & lower));
-    for (uint32_t r = (0u - cross) & cross; r; r = (r - cross) & cross) sw.item[o++] = (uint16_t)(lane | (r << 6));
-    wave_lds_fence();
-    for (uint32_t q0 = 0; q0 < total; q0 += 64) {
-        const uint32_t q = q0 + lane, e = q < total ? sw.item[q] : lane, r = e >> 6;
-        const int owner = (int)(e & 63u);
-        const int x = __shfl(lx, owner), y = __shfl(ly, owner), z = __shfl(lz, owner);
-        if (r)
-            sw.region[r][owner] =
-                region_word(acc.resolve(x + (int)(r & 1u), y + (int)((r >> 1) & 1u), z + (int)(r >> 2)));
-    }
-    wave_lds_fence();
-    // the rows' pairs, then what a row holds in the next region
-    const int x0 = sx ? 6 : i & 7;
-    uint64_t h[4];
-    int a[4];
-    typedef float f32x2 __attribute__((ext_vector_type(2), aligned(4)));
-    f32x2 v[4];
-    float c[8], w[4];
+    const uint64_t crossing = __ballot(cross != 0u);
+    float c[8];
+    if (crossing == 0) {
+        // every footprint of the wave in one region
+        if (own & 1u) {
+            GlobalFloat* const q = region_values(own) + ((i & 7) + 8 * (j & 7) + 64 * (k & 7));
 #pragma unroll
-    for (int row = 0; row < 4; ++row) h[row] = sw.region[cross & ((uint32_t)row << 1)][lane];
+            for (int row = 0; row < 4; ++row) {
+                const f32x2 v = *(GlobalPair*)(q + 8 * (row & 1) + 64 * (row >> 1));
+                c[2 * row] = v.x;
+                c[2 * row + 1] = v.y;
+            }
+        } else {
+            const float v = *region_values(own);
 #pragma unroll
-    for (int row = 0; row < 4; ++row) {
-        // one value (a tile, the background) is read as the second of a pair:
-        // the buffer's header is ahead of it
-        a[row] = 8 * ((j + (row & 1)) & 7) + 64 * ((k + (row >> 1)) & 7);
-        v[row] = *reinterpret_cast<const __attribute__((address_space(1))) f32x2*>(
-            region_values(h[row]) + ((h[row] & 1u) ? a[row] + x0 : -1));
-        w[row] = 0.0f;
-    }
-    if (sx) {
+            for (int q = 0; q < 8; ++q) c[q] = v;
+        }
+    } else {
+        // 1, 3 or 7 further regions: the non-empty subsets of the crossed axes
+        uint32_t mine = cross;
+        int head = (int)lane;
+        uint64_t m1 = crossing, m2 = __ballot((mine & (mine - 1u)) != 0u), m4 = __ballot(mine == 7u);
+        uint32_t total = (uint32_t)(__popcll(m1) + 2 * __popcll(m2) + 4 * __popcll(m4));
+        if (total >= 64) {
+            // ordered positions: lanes in a row with one leaf share its first
+            // lane's descents, for the axes that any of them crosses
+            const uint64_t c1 = __ballot(cross & 1u), c2 = __ballot(cross & 2u), c4 = __ballot(cross & 4u);
+            const int bx = __shfl_up(lx, 1), by = __shfl_up(ly, 1), bz = __shfl_up(lz, 1);
+            const uint64_t heads = __ballot(lane == 0u || bx != lx || by != ly || bz != lz);
+            const uint64_t above = ~1ull << lane;   // lanes past this one
+            head = 63 - __clzll((long long)(heads & ~above));
+            const uint64_t later = heads & above, run = (later ? (later & (0ull - later)) - 1u : ~0ull) & (~0ull << head);
+            mine = head != (int)lane ? 0u : ((c1 & run) ? 1u : 0u) | ((c2 & run) ? 2u : 0u) | ((c4 & run) ? 4u : 0u);
+            m1 = __ballot(mine != 0u);
+            m2 = __ballot((mine & (mine - 1u)) != 0u);
+            m4 = __ballot(mine == 7u);
+            total = (uint32_t)(__popcll(m1) + 2 * __popcll(m2) + 4 * __popcll(m4));
+        }
+        const uint64_t lower = (1ull << lane) - 1u;
+        uint32_t o = (uint32_t)(__popcll(m1 & lower) + 2 * __popcll(m2 & lower) + 4 * __popcll(m4 & lower));
+        for (uint32_t r = (0u - mine) & mine; r; r = (r - mine) & mine) sw.item[o++] = (uint16_t)(lane | (r << 6));
+        // the lower node, or the constant in its place | 1
+        const uint64_t node =
+            acc.cnode ? reinterpret_cast<uint64_t>(acc.cnode) : reinterpret_cast<uint64_t>(acc.cconst) | 1u;
+        wave_lds_fence();
+        for (uint32_t q0 = 0; q0 < total; q0 += 64) {
+            const uint32_t q = q0 + lane, e = q < total ? sw.item[q] : lane, r = e >> 6;
+            const int owner = (int)(e & 63u);
+            const int x = __shfl(lx, owner), y = __shfl(ly, owner), z = __shfl(lz, owner);
+            const uint64_t found = __shfl((unsigned long long)node, owner);
+            if (r) {
+                VdbAcc from{view};
+                from.reset();
+                from.cLx = x >> 4;
+                from.cLy = y >> 4;
+                from.cLz = z >> 4;
+                from.cnode = (found & 1u) ? nullptr : (const Word*)reinterpret_cast<GlobalWord*>(found);
+                from.cconst = (const float*)region_values(found);
+                sw.region[r - 1][owner] =
+                    region_word(from.resolve(x + (int)(r & 1u), y + (int)((r >> 1) & 1u), z + (int)(r >> 2)));
+            }
+        }
+        wave_lds_fence();
+        // the rows' pairs, then what a row holds in the next region
+        const int x0 = sx ? 6 : i & 7;
+        uint64_t h[4];
+        int a[4];
+        f32x2 v[4];
+        float w[4];
 #pragma unroll
         for (int row = 0; row < 4; ++row) {
-            const uint64_t h1 = sw.region[(cross & ((uint32_t)row << 1)) | 1u][lane];
-            w[row] = region_values(h1)[(h1 & 1u) ? a[row] : 0];
+            const uint32_t r = cross & ((uint32_t)row << 1);
+            h[row] = r ? sw.region[r - 1][head] : own;
         }
-    }
 #pragma unroll
-    for (int row = 0; row < 4; ++row) {
-        c[2 * row] = (h[row] & 1u) && !sx ? v[row].x : v[row].y;
-        c[2 * row + 1] = sx ? w[row] : v[row].y;
+        for (int row = 0; row < 4; ++row) {
+            // one value (a tile, the background) is read as the second of a pair:
+            // the buffer's header is ahead of it
+            a[row] = 8 * ((j + (row & 1)) & 7) + 64 * ((k + (row >> 1)) & 7);
+            v[row] = *(GlobalPair*)(region_values(h[row]) + ((h[row] & 1u) ? a[row] + x0 : -1));
+            w[row] = 0.0f;
+        }
+        if (sx) {
+#pragma unroll
+            for (int row = 0; row < 4; ++row) {
+                const uint64_t h1 = sw.region[cross & ((uint32_t)row << 1)][head];
+                w[row] = region_values(h1)[(h1 & 1u) ? a[row] : 0];
+            }
+        }
+#pragma unroll
+        for (int row = 0; row < 4; ++row) {
+            c[2 * row] = (h[row] & 1u) && !sx ? v[row].x : v[row].y;
+            c[2 * row + 1] = sx ? w[row] : v[row].y;
+        }
     }
     const float fx = px - fx0, fy = py - fy0, fz = pz - fz0;
     const float c00 = lerp(c[0], c[1], fx), c10 = lerp(c[2], c[3], fx);
