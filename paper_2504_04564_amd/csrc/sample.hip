@@ -14,7 +14,7 @@ __global__ __launch_bounds__(kBlock) void sample_kernel(View view, const float* 
 {
     Acc acc{view};
     acc.reset();
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = (uint64_t)wide_block() * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
     out[i] = filter ? trilinear(acc, x, y, z) : nearest(acc, x, y, z);
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kBlock) void sample_tree_kernel(VdbView view, const
     __shared__ SampleWave waves[kBlock / 64];
     SampleWave& sw = waves[threadIdx.x >> 6];
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t id = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, at = id < n ? id : n - 1;
+    const uint64_t id = (uint64_t)wide_block() * blockDim.x + threadIdx.x, at = id < n ? id : n - 1;
     const float px = __builtin_amdgcn_fmed3f(pos[3 * at], -2.0f, (float)view.nx + 1.0f);   // as trilinear()
     const float py = __builtin_amdgcn_fmed3f(pos[3 * at + 1], -2.0f, (float)view.ny + 1.0f);
     const float pz = __builtin_amdgcn_fmed3f(pos[3 * at + 2], -2.0f, (float)view.nz + 1.0f);
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kBlock) void lookup_kernel(VdbView view, const int3
 {
     VdbAcc acc{view};
     acc.reset();
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = (uint64_t)wide_block() * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int x = ijk[3 * i], y = ijk[3 * i + 1], z = ijk[3 * i + 2];
     // voxels beyond the volume read B (edge leaves store B there, regions
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void compare_fold_kernel(const double* __restr
 __global__ void philox_kernel(const uint32_t* __restrict__ ctr, const uint32_t* __restrict__ key,
                               uint64_t n, uint32_t* __restrict__ out)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t i = (uint64_t)wide_block() * blockDim.x + threadIdx.x;
     if (i >= n) return;
     uint32_t c0 = ctr[4 * i], c1 = ctr[4 * i + 1], c2 = ctr[4 * i + 2], c3 = ctr[4 * i + 3];
     philox4x32_10(c0, c1, c2, c3, key[2 * i], key[2 * i + 1]);
@@ -303,7 +303,7 @@ extern "C" vdbc_status vdbc_sample(const vdbc_grid* g, const float* pos, uint64_
     if (s) return s;
     if ((s = check_samples(pos, n, filter, out))) return s;
     if (n == 0) return VDBC_OK;
-    const dim3 grid((unsigned)((n + kBlock - 1) / kBlock));
+    const dim3 grid = wide_grid((n + kBlock - 1) / kBlock);
     if (filter)
         hipLaunchKernelGGL(sample_tree_kernel, grid, dim3(kBlock), 0, static_cast<hipStream_t>(stream), v, pos, n, out);
     else
@@ -323,7 +323,7 @@ extern "C" vdbc_status vdbc_sample_dense(const float* dense, vdbc_dims d, float 
     if ((s = check_samples(pos, n, filter, out))) return s;
     if (n == 0) return VDBC_OK;
     hipLaunchKernelGGL((sample_kernel<DenseAcc, DenseView>),
-                       dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                       wide_grid((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
                        static_cast<hipStream_t>(stream), v, pos, n, (int)filter, out);
     return launch_check("vdbc_sample_dense");
 }
@@ -338,7 +338,7 @@ extern "C" vdbc_status vdbc_lookup(const vdbc_grid* g, const int32_t* ijk, uint6
     if (n && (!ijk || !out)) return fail(VDBC_E_INVALID, "null coordinates or output");
     if (n > (uint64_t)0x7FFFFFFFull * kBlock) return fail(VDBC_E_INVALID, "too many lookups");
     if (n == 0) return VDBC_OK;
-    hipLaunchKernelGGL(lookup_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+    hipLaunchKernelGGL(lookup_kernel, wide_grid((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
                        static_cast<hipStream_t>(stream), v, ijk, n, out);
     return launch_check("vdbc_lookup");
 }
@@ -391,7 +391,7 @@ extern "C" vdbc_status vdbc_philox(const uint32_t* ctr, const uint32_t* key, uin
     if (n && (!ctr || !key || !out)) return fail(VDBC_E_INVALID, "null argument");
     if (n > (uint64_t)0x7FFFFFFFull * kBlock) return fail(VDBC_E_INVALID, "too many counters");
     if (n == 0) return VDBC_OK;
-    hipLaunchKernelGGL(philox_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+    hipLaunchKernelGGL(philox_kernel, wide_grid((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
                        static_cast<hipStream_t>(stream), ctr, key, n, out);
     return launch_check("vdbc_philox");
 }
