@@ -197,81 +197,103 @@ __global__ __launch_bounds__(kBlock) void majorant_tree_kernel(VdbView view, Med
 }
 
 // Dense array.  A workgroup takes a run of macrocells along x, 256 voxels at
-// most: a lane reads its column of the run's (C+2)^2 rows (256 contiguous bytes
-// a wave and row), six rows in flight; the cells fold the columns in LDS.  The
-// columns before and after the run are read by all threads, a row each.  Bound
-// by the array's bytes, (C+2)^2 / C^2 times.  (A thread per row of a cell's own
-// footprint read 72-byte rows, column by column: 364 us at 512^3 with cells of
-// 16; 129 us so, where the array at the copy rate takes 113.)
+// most: 2^wl lanes read a row of the run (contiguous, a wave and row 256 bytes
+// of it), the others its further rows, and a thread has six rows in flight; the
+// cells fold the columns in LDS.  NARROW: less than a wave reads a row, and the
+// wave folds its rows first.  Bound by the array's bytes, (C+2)^2 / C^2 times.
+// (A thread per row of a cell's own footprint read 72-byte rows, column by
+// column: 362 us at 512^3 with cells of 16; 122 us so, where the array at the copy
+// rate takes 113.  Rows outside the volume read again and 64 lanes a row for 16
+// voxels: 16 x 900 x 900 with cells of 8 62 us by the thread's rows, 78 then, 36 so;
+// 900 x 900 x 16 with cells of 64 126, 214 and 50.)
+template <bool NARROW>
 __global__ __launch_bounds__(kBlock) void majorant_dense_kernel(DenseView view, MediumK m, int C, int gx, int gy, int gz,
-                                                                int run, int runs, float* __restrict__ out)
+                                                                int run, int runs, int wl, float* __restrict__ out)
 {
-    __shared__ float col[2][kBlock + 2][4];   // min, max of the run's columns, from the one before it; by row set
+    __shared__ float col[2][kBlock];   // min, max of the run's columns, by row set
     __shared__ float ends[2][2][kBlock / 64];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int width = run * C, chunks = (width + 63) / 64, sets = chunks == 1 ? 4 : chunks == 2 ? 2 : 1;
     const uint32_t blk = wide_block();
     const int rx = (int)(blk % (unsigned)runs), cy = (int)((blk / (unsigned)runs) % (unsigned)gy),
               cz = (int)(blk / ((unsigned)runs * (unsigned)gy));
     if (cz >= gz) return;   // the whole workgroup
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int width = run * C, lanes = 1 << wl, sets = kBlock >> wl;
     const int E = C + 2, x0 = rx * width, y0 = C * cy - 1, z0 = C * cz - 1;
-    const int64_t sy = view.nx, sz = (int64_t)view.nx * view.ny;
     const float B = view.background;
-    // rows outside the volume read B; in its place one of the footprint's own
-    // rows is read again and B enters below
-    const bool rows_out = y0 < 0 || z0 < 0 || y0 + E > view.ny || z0 + E > view.nz;
-    const int chunk = sets == 4 ? 0 : sets == 2 ? wave & 1 : wave, set = sets == 4 ? wave : sets == 2 ? wave >> 1 : 0;
-    const int c = 64 * chunk + lane, x = x0 + c;
-    float vmin = rows_out ? B : INFINITY, vmax = rows_out ? B : -INFINITY;
-    if (chunk < chunks && x < view.nx) {
-        const float* const base = view.data + x;
-        const int nj = (E + sets - 1) / sets;
-        for (int k = 0; k < E; ++k) {
-            const float* const plane = base + sz * min(max(z0 + k, 0), view.nz - 1);
-            for (int j = 0; j < nj; j += 6) {
+    // the footprint's rows inside the volume; B stands for those outside
+    const int ya = max(y0, 0), za = max(z0, 0), ny = min(y0 + E, view.ny) - ya,
+              nz = min(z0 + E, view.nz) - za, rows = ny * nz;
+    const bool rows_out = rows < E * E;
+    const uint32_t inv = ((1u << 20) + (uint32_t)ny - 1u) / (uint32_t)ny;   // r / ny = r inv >> 20 for r < 66^2
+    const auto row_at = [&](int r) {
+        const int k = (int)(((uint32_t)r * inv) >> 20);
+        return view.data + (int64_t)view.nx * ((ya + r - k * ny) + (int64_t)view.ny * (za + k));
+    };
+    const int c = t & (lanes - 1), x = x0 + c, set = NARROW ? t >> wl : __builtin_amdgcn_readfirstlane(t >> wl);
+    float vmin = INFINITY, vmax = -INFINITY;
+    if (x >= view.nx) {
+        vmin = vmax = B;
+    } else if (NARROW) {
+        for (int r = set; r < rows; r += 6 * sets) {
+            float v[6];
+#pragma unroll
+            for (int u = 0; u < 6; ++u) v[u] = row_at(min(r + u * sets, rows - 1))[x];
+#pragma unroll
+            for (int u = 0; u < 6; ++u) {
+                vmin = fminf(vmin, v[u]);
+                vmax = fmaxf(vmax, v[u]);
+            }
+        }
+    } else {
+        // (a plane at a time: the rows' addresses are scalar and cost little)
+        const float* plane = view.data + x + (int64_t)view.nx * (ya + (int64_t)view.ny * za);
+        for (int k = 0; k < nz; ++k, plane += (int64_t)view.nx * view.ny)
+            for (int j = set; j < ny; j += 6 * sets) {
                 float v[6];
 #pragma unroll
-                for (int u = 0; u < 6; ++u) {
-                    const int row = min((j + u) * sets + set, E - 1);
-                    v[u] = plane[sy * min(max(y0 + row, 0), view.ny - 1)];
-                }
+                for (int u = 0; u < 6; ++u) v[u] = plane[(int64_t)view.nx * min(j + u * sets, ny - 1)];
 #pragma unroll
                 for (int u = 0; u < 6; ++u) {
                     vmin = fminf(vmin, v[u]);
                     vmax = fmaxf(vmax, v[u]);
                 }
             }
-        }
-    } else {
-        vmin = vmax = B;
     }
-    if (chunk < chunks) {
-        col[0][c + 1][set] = vmin;
-        col[1][c + 1][set] = vmax;
+    if (NARROW)
+        for (int o = 32; o >= lanes; o >>= 1) {
+            vmin = fminf(vmin, __shfl_xor(vmin, o));
+            vmax = fmaxf(vmax, __shfl_xor(vmax, o));
+        }
+    const int kept = NARROW ? kBlock / 64 : sets;   // row sets in LDS
+    if (!NARROW || lane < lanes) {
+        col[0][(NARROW ? wave : set) * lanes + c] = vmin;
+        col[1][(NARROW ? wave : set) * lanes + c] = vmax;
     }
     // the columns x0 - 1 and x0 + width
-    float e0[2] = {INFINITY, INFINITY}, e1[2] = {-INFINITY, -INFINITY};
-    for (int r = t; r < E * E; r += kBlock) {
-        const int64_t row = sy * min(max(y0 + r % E, 0), view.ny - 1) + sz * min(max(z0 + r / E, 0), view.nz - 1);
+    const int xe[2] = {x0 - 1, x0 + width};
+    const bool in[2] = {xe[0] >= 0, xe[1] < view.nx};
+    float e[2][2] = {{in[0] ? INFINITY : B, in[0] ? -INFINITY : B}, {in[1] ? INFINITY : B, in[1] ? -INFINITY : B}};
+    if (in[0] || in[1])
+        for (int r = t; r < rows; r += kBlock) {
+            const float* const row = row_at(r);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int xe = s ? x0 + width : x0 - 1;
-            const float v = xe < 0 || xe >= view.nx ? B : view.data[row + xe];
-            e0[s] = fminf(e0[s], v);
-            e1[s] = fmaxf(e1[s], v);
+            for (int s = 0; s < 2; ++s) {
+                const float v = in[s] ? row[xe[s]] : B;
+                e[s][0] = fminf(e[s][0], v);
+                e[s][1] = fmaxf(e[s][1], v);
+            }
         }
-    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            e0[s] = fminf(e0[s], __shfl_xor(e0[s], o));
-            e1[s] = fmaxf(e1[s], __shfl_xor(e1[s], o));
+            e[s][0] = fminf(e[s][0], __shfl_xor(e[s][0], o));
+            e[s][1] = fmaxf(e[s][1], __shfl_xor(e[s][1], o));
         }
     if (lane == 0)
         for (int s = 0; s < 2; ++s) {
-            ends[0][s][wave] = e0[s];
-            ends[1][s][wave] = e1[s];
+            ends[0][s][wave] = e[s][0];
+            ends[1][s][wave] = e[s][1];
         }
     __syncthreads();
     const int cx = rx * run + t;
@@ -283,10 +305,13 @@ __global__ __launch_bounds__(kBlock) void majorant_dense_kernel(DenseView view, 
                 lo = fminf(lo, ends[0][q != 0][w]);
                 hi = fmaxf(hi, ends[1][q != 0][w]);
             }
+        } else if (q > lanes) {   // past the volume
+            lo = fminf(lo, B);
+            hi = fmaxf(hi, B);
         } else {
-            for (int w = 0; w < sets; ++w) {
-                lo = fminf(lo, col[0][q][w]);
-                hi = fmaxf(hi, col[1][q][w]);
+            for (int w = 0; w < kept; ++w) {
+                lo = fminf(lo, col[0][w * lanes + q - 1]);
+                hi = fmaxf(hi, col[1][w * lanes + q - 1]);
             }
         }
     }
@@ -1016,10 +1041,24 @@ static vdbc_status launch_majorant(const DenseView& v, const MediumK& m, uint32_
     uint64_t cells;
     vdbc_status s = majorant_cells(v.nx, v.ny, v.nz, C, g, &cells);
     if (s) return s;
-    // 64, 128 or 256 voxels of cells: narrow volumes leave no wave idle
-    const int width = v.nx <= 64 ? 64 : v.nx <= 128 ? 128 : 256, run = width / (int)C, runs = (g[0] + run - 1) / run;
-    hipLaunchKernelGGL(majorant_dense_kernel, wide_grid((uint64_t)runs * g[1] * g[2]), dim3(kBlock), 0, st, v, m, (int)C, g[0],
-                       g[1], g[2], run, runs, out);
+    // 256, 128 or 64 voxels of cells: fewer where the volume is narrower, or where
+    // workgroups would be too few for the card (cells of 64 at 512^3: 437 us with
+    // 128 workgroups of 256 voxels, 223 with 512 of 64)
+    int width = 256, run = 0, runs = 0;
+    for (;; width /= 2) {
+        run = width / (int)C;
+        runs = (g[0] + run - 1) / run;
+        if (width == 64 || (v.nx > width / 2 && (uint64_t)runs * g[1] * g[2] >= 512)) break;
+    }
+    int wl = 4;   // lanes a row
+    while (wl < 8 && (1 << wl) < std::min(run * (int)C, v.nx)) ++wl;
+    const dim3 grid = wide_grid((uint64_t)runs * g[1] * g[2]);
+    if (wl < 6)
+        hipLaunchKernelGGL(majorant_dense_kernel<true>, grid, dim3(kBlock), 0, st, v, m, (int)C, g[0], g[1], g[2], run, runs,
+                           wl, out);
+    else
+        hipLaunchKernelGGL(majorant_dense_kernel<false>, grid, dim3(kBlock), 0, st, v, m, (int)C, g[0], g[1], g[2], run, runs,
+                           wl, out);
     return launch_check("majorant");
 }
 

@@ -1,0 +1,32 @@
+"""Majorants of dense arrays that are narrow, flat or both: rows of less than a
+wave, footprints mostly outside the volume, and launches of few workgroups.
+Equal bit for bit to the largest extinction over each footprint."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_04564_amd import _build, vdbc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    _build.ensure_built()
+    return vdbc.load()
+
+
+@pytest.mark.parametrize("nx", [1, 2, 15, 16, 17, 32, 33, 63, 100, 257])
+@pytest.mark.parametrize("ny,nz", [(1, 1), (1, 70), (70, 1), (66, 3), (130, 129)])
+@pytest.mark.parametrize("C", [4, 7, 16, 33, 64])
+def test_every_footprint(nx, ny, nz, C):
+    rng = np.random.default_rng(nx * ny + nz + C)
+    v = torch.from_numpy(rng.random((nz, ny, nx), dtype=np.float32)).cuda()
+    # extinction = value: a cell's majorant is its footprint's largest value, the background 0.75 around the volume
+    med = dict(sigma_scale=float(max(nx, ny, nz)), tf=[(1.0, 1.0, 1.0, 0.0), (1.0, 1.0, 1.0, 1.0)], tf_range=(0.0, 1.0))
+    got = vdbc.majorant(v, med, C, 0.75)
+    g = [-(-n // C) for n in (nz, ny, nx)]
+    padded = torch.full([C * q + 2 for q in g], 0.75, device="cuda")
+    padded[1:nz + 1, 1:ny + 1, 1:nx + 1] = v
+    want = torch.nn.functional.max_pool3d(padded[None, None], C + 2, C)[0, 0]
+    assert torch.equal(got, want)
