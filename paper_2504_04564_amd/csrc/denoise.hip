@@ -1322,13 +1322,15 @@ vdbc_status conv_fwd(const ConvIn& in, int stride, const uint16_t* w, const floa
     else if (cout <= 32)
         hipLaunchKernelGGL((conv_fwd_kernel<2, kConvTiles>), dim3(gb), dim3(kThreads), 0, st, in, w, bias, cout,
                            stride, ho, wo, relu, out_bf, out_f, resid);
-    // four channel tiles: as many pixel tiles a wave as leave four workgroups a CU
-    // (32 -> 64 channels, stride 2: 8 x 256^2 in 33 us with four tiles, 30 with two;
-    // 512^2 in 25.8 with four, 19.8 with one)
-    else if (gb >= 1024)
+    // four channel tiles.  More pixel tiles a wave share its weights, fewer leave
+    // more waves and registers: four only where there are many weights and enough
+    // workgroups, one where the whole layer is small (stride 2, us with four, two
+    // and one: 64 -> 64 channels 8 x 256^2 48, 58, 87, 512^2 35, 33, 46 and 256^2
+    // 32, 22, 17; 32 -> 64 8 x 512^2 105, 91, 112, 512^2 24, 17, 19, 256^2 21, 13, 9.6)
+    else if (in.ca + in.cb > 48 && gb >= 512)
         hipLaunchKernelGGL((conv_fwd_kernel<4, kConvTiles>), dim3(gb), dim3(kThreads), 0, st, in, w, bias, cout,
                            stride, ho, wo, relu, out_bf, out_f, resid);
-    else if (gb >= 512)
+    else if (gb >= 512 || gb * (unsigned)(in.ca + in.cb) > 5000)
         hipLaunchKernelGGL((conv_fwd_kernel<4, 2>), dim3(blocks(P, 128)), dim3(kThreads), 0, st, in, w, bias, cout,
                            stride, ho, wo, relu, out_bf, out_f, resid);
     else
