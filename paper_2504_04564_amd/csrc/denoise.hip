@@ -240,11 +240,13 @@ __device__ __forceinline__ void stage_window(uint4* s_tile, int n, int cg, const
     constexpr int U = 6;
     const bool pow2 = (cg & (cg - 1)) == 0;
     const int shift = 31 - __clz(cg);
-    for (int e0 = threadIdx.x; e0 < n; e0 += U * kThreads) {
+    for (int base = 0; base < n; base += U * kThreads) {
+        const int e0 = base + (int)threadIdx.x;
         uint4 v[U];
         int at[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (base + u * kThreads >= n) break;   // all threads: 8 channels are one or two loads long, not six
             const int e = min(e0 + u * kThreads, n - 1);
             const int pix = pow2 ? e >> shift : e / cg, c8 = e - pix * cg;
             at[u] = pix * (cg + 1) + c8;
