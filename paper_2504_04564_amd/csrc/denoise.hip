@@ -284,26 +284,36 @@ __device__ __forceinline__ void conv_tile_accumulate(const uint4* s_tile, const 
 #pragma unroll
         for (int m = 0; m < 4; ++m) a[m] = ((row0 + (m >> 1)) * IW + (m & 1) * 16 + col0) * ps + g;
         // the chunks come in threes (9 cin / 32); four channel tiles have no
-        // registers for more than one ahead
-        constexpr int D = NT <= 2 ? 3 : 1;
+        // registers for loads ahead: one chunk ahead took a workgroup of four off
+        // the CU (48 -> 48 channels at 8 x 256^2 55 us, 51 without)
+        constexpr bool AHEAD = NT <= 2;
+        constexpr int D = AHEAD ? 3 : 1;
         bf16x8 Bn[D][NT];
+        if (AHEAD) {
 #pragma unroll
-        for (int u = 0; u < D; ++u)
+            for (int u = 0; u < D; ++u)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) Bn[u][t] = load8(w + 32 * u + b[t]);
+                for (int t = 0; t < NT; ++t) Bn[u][t] = load8(w + 32 * u + b[t]);
+        }
         int c = 0, kx = 0, tap_off = 0;
         for (int kb = 0; kb < K; kb += 32 * D) {
 #pragma unroll
             for (int u = 0; u < D; ++u) {
                 bf16x8 B[NT], A[4];
+                if (!AHEAD) {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) B[t] = load8(w + kb + b[t]);
+                }
                 const int off = (MIRROR ? -tap_off : tap_off) + c / 8;
 #pragma unroll
                 for (int m = 0; m < 4; ++m) A[m] = __builtin_bit_cast(bf16x8, s_tile[a[m] + off]);
-                const uint16_t* const wn = w + min(kb + 32 * (u + D), K - 32);
+                if (AHEAD) {
+                    const uint16_t* const wn = w + min(kb + 32 * (u + D), K - 32);
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    B[t] = Bn[u][t];
-                    Bn[u][t] = load8(wn + b[t]);
+                    for (int t = 0; t < NT; ++t) {
+                        B[t] = Bn[u][t];
+                        Bn[u][t] = load8(wn + b[t]);
+                    }
                 }
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
@@ -612,8 +622,10 @@ __device__ __forceinline__ void dgrad_store_staged(float* s_out, const float4 (&
 // LDS, and tap (ky, kx) of input pixel (y, x) reads dz at (y + 1 - ky,
 // x + 1 - kx), a shifted view of the window.  Same contraction order,
 // operands and epilogue as conv_dgrad_kernel.
+// (Four channel tiles: the registers of four workgroups a CU, not three.  64 -> 32
+// channels at 8 x 256^2 50 -> 45 us.)
 template <int NT, bool STAGED>
-__global__ __launch_bounds__(kThreads) void conv_dgrad_tiled_kernel(const uint16_t* __restrict__ dz, int coutp,
+__global__ __launch_bounds__(kThreads, NT == 4 && STAGED ? 4 : 1) void conv_dgrad_tiled_kernel(const uint16_t* __restrict__ dz, int coutp,
                                                                     int ho, int wo,
                                                                     const uint16_t* __restrict__ wt, int cin,
                                                                     DgradOut o)
