@@ -34,8 +34,8 @@ __device__ __forceinline__ float majorant_of(const MediumK& m, float vmin, float
     return m.ds * a;
 }
 
-// VDB.  The 8^3 blocks of the footprint (at most 11^3, for a macrocell of 64;
-// 4^3 up to 16) are resolved one per thread: a tile or an empty region enters
+// VDB.  The 8^3 blocks of the footprint (at most 10^3: the 66 voxels of a
+// macrocell of 64 from the last of a block on; 4^3 up to 16) are resolved one per thread: a tile or an empty region enters
 // the min and max at once, a stored leaf is queued in LDS, whole leaves at the
 // front and the slices of a border at the back.  A whole leaf is two 16-byte
 // loads a lane, two leaves at a time; eight borders, 64 values or fewer each,
@@ -44,7 +44,8 @@ __device__ __forceinline__ float majorant_of(const MediumK& m, float vmin, float
 // one resolved.  (One leaf at a time, eight masked 4-byte loads for a border
 // too: 186 us at 512^3 with cells of 16, 702 us at 994x676x1225 with 64; 44 and
 // 125 us so.  The leaves' bytes at the copy rate are 11 and 70 us.)
-constexpr int kMajorantQueue = 11 * 11 * 11;
+constexpr int kMajorantQueue = 10 * 10 * 10;
+static_assert((7 + 64 + 2 + 7) / 8 == 10, "blocks an axis of the largest macrocell");
 constexpr int kMajorantWaveCell = 16;
 
 struct MajorantShared {

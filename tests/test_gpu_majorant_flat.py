@@ -30,3 +30,12 @@ def test_every_footprint(nx, ny, nz, C):
     padded[1:nz + 1, 1:ny + 1, 1:nx + 1] = v
     want = torch.nn.functional.max_pool3d(padded[None, None], C + 2, C)[0, 0]
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("C", [17, 33, 57, 63, 64])
+def test_footprints_of_the_most_leaves(C):
+    # every region of an inner cell's footprint is a stored leaf, 10^3 of them with cells of 57 and more
+    v = np.random.default_rng(C).random((200, 197, 203), dtype=np.float32)
+    med = dict(sigma_scale=6.0, tf=[(1.0, 1.0, 1.0, 0.0), (1.0, 1.0, 1.0, 1.0)], tf_range=(0.0, 1.0))
+    g = vdbc.Grid(vdbc.encode(v, 1.0, flags=vdbc.BG_EXPLICIT)[0])
+    assert torch.equal(vdbc.majorant(g, med, C), vdbc.majorant(torch.from_numpy(v).cuda(), med, C, 0.0))
