@@ -182,13 +182,20 @@ __device__ __forceinline__ int cell_exit(const Flight& f, float edge, const int 
     return axis;
 }
 
-// -log(x) for x in [2^-24, 1], bit for bit __logf's: its scaling of denormals
-// and its infinities left out.
+// -log(x) = -ln 2 log2(x) for x in [2^-24, 1], with the hardware's log2.  ln 2 =
+// 0x1.62e42fefa39ef...p-1 is split into its first 24 bits and the next 24, and the
+// rounding of the head's product is recovered by an fma (Dekker's double-length
+// product, Numer. Math. 18, 1971, in the form with one fma).  The last fma rounds
+// once from the exact product, so the recovered part enters a second time, below
+// half a unit of the last place; it stays because every image depends on the bits.
+// On this range they are __logf's, whose care for denormals and infinities costs
+// the kernel 4 to 11 % (512^3 frame 5.42 -> 5.62 ms, 994x676x1225 15.9 -> 17.9).
 __device__ __forceinline__ float neg_log(float x)
 {
-    const float y = __builtin_amdgcn_logf(x), c = __uint_as_float(0x3F317217u), cc = __uint_as_float(0x3377D1CFu);
-    const float e = fmaf(y, cc, fmaf(y, c, -(y * c)));
-    return -fmaf(y, c, e);
+    const float head = 0x1.62e42ep-1f, tail = 0x1.efa39ep-25f;
+    const float y = __builtin_amdgcn_logf(x);
+    const float e = fmaf(y, tail, fmaf(y, head, -(y * head)));
+    return -fmaf(y, head, e);
 }
 
 // Advances the flight to its next tentative collision: returns 1 with f.t
