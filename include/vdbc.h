@@ -252,7 +252,8 @@ enum {
                                       from the root) */
     VDBC_RENDER_CACHE_LEAF = 32u,  /* PT, VDB: cache the last leaf only (default, neither
                                       flag: the last leaf and the last lower node).  The
-                                      image does not depend on the cache policy. */
+                                      image does not depend on the cache policy.  With
+                                      either flag VDBC_RENDER_INDEX has no effect there. */
     VDBC_RENDER_INDEX = 128u,      /* VDB: build an index of the leaf regions in the workspace
                                       first (4 bytes per 8^3 voxels, rebuilt by every call)
                                       and read the tree through it.  The image does not
@@ -288,8 +289,9 @@ typedef struct {
                                depend on it */
     float iso;              /* ISO: iso value */
     uint32_t refine;        /* ISO: bisection steps on the crossing interval (<= 64) */
-    uint32_t chunk_spp;     /* PT work split: 0 or >= spp: one work item per 256-pixel
-                               tile (all its samples); otherwise each tile is split into
+    uint32_t chunk_spp;     /* PT work split: 0 (without VDBC_RENDER_SPLIT) or >= spp: one
+                               work item per 256-pixel tile (all its samples); 0 with
+                               VDBC_RENDER_SPLIT: the library's choice; otherwise each tile is split into
                                ceil(spp / chunk_spp) work items of chunk_spp samples
                                (the last one shorter) that different workgroups run,
                                and the tiles' fixed-point sums meet in the workspace

@@ -4,11 +4,10 @@ Times every candidate of a small search space on the device (one warm-up,
 median of `reps` HIP-event timings) and keeps the fastest; choices are
 persisted to a JSON file keyed by workload class so later runs reuse them.
 Candidates only change launch geometry (wave tile shape, samples per work
-item, order of the tiles in the work queue, persistent grid size), the VDB
-accessor's per-thread cache policy
-(none, last leaf, last leaf and last lower node) or the majorant cell size;
-all but the cell size leave
-every image bit-identical, the cell size changes the estimator's random
+item, order of the tiles in the work queue, persistent grid size), how a VDB is
+read (through its tree without a per-thread cache or with the last leaf cached,
+or through the region index) or the majorant cell size; all but the cell size
+leave every image bit-identical, the cell size changes the estimator's random
 stream but not its expectation.
 """
 from __future__ import annotations
@@ -23,8 +22,8 @@ from . import vdbc
 
 RENDER_SPACE = {"macrocell": (8, 16, 32, 64), "tile_w": (8, 16, 32, 64), "cache": (0, 1, 2),
                 "chunk_spp": (0, 4, 8, 16)}
-# the cost order of the work queue is tried on this many of the fastest
-# raster-order candidates (a second stage instead of doubling the grid)
+# the cost order of the work queue is asked for on this many of the fastest
+# candidates without it (a second stage instead of doubling the grid)
 ORDER_STAGE = 8
 BATCH_SPACE = {"macrocell": (8, 16, 32, 64), "tile_w": (8, 16, 32), "blocks_per_cu": (2, 4, 8),
                "persistent": (1,), "chunk_spp": (0, 1, 2, 4)}
@@ -69,14 +68,16 @@ def save(path: str, table: dict):
 def tune_render(field, camera: dict, medium: dict, params: dict, background=None,
                 space: dict | None = None, reps: int = 5):
     """Best (macrocell, tile_w, cache, chunk_spp, order) for a path-traced
-    frame; returns (best, all).  The cache policy is searched for VDB grids
-    only; work-item sizes of spp samples or more are the same launch as 0 and
-    are skipped; the cost order (order 1) is timed on the ORDER_STAGE fastest
-    raster-order (order 0) candidates."""
+    frame; returns (best, all).  cache (VDB grids only): 0 no cache, 1 the last
+    leaf, 2 the region index.  chunk_spp: 0 the library's choice of work items
+    and of their order, spp whole tiles, else samples per work item; an entry 0
+    of the space stands for the first two, and entries of spp samples or more
+    are skipped.  order 1: RENDER_COST_ORDER, timed on the ORDER_STAGE fastest
+    candidates; order 0: the tiles in raster order, unless the library chose."""
     space = dict(RENDER_SPACE, **(space or {}))
     caches = space["cache"] if isinstance(field, vdbc.Grid) else (2,)
     spp = params.get("spp", 1)
-    chunks = [c for c in space["chunk_spp"] if c == 0 or c < spp]
+    chunks = [q for c in space["chunk_spp"] for q in ((0, spp) if c == 0 else (c,)) if c == 0 or c < spp]
     results = []
     for C_ in space["macrocell"]:
         for tw in space["tile_w"]:

@@ -21,7 +21,7 @@ BG_EXPLICIT, NO_CORNERS, NO_PRUNE, PARTIAL = 1, 2, 4, 8
 MODE_EA, MODE_PT, MODE_ISO = 0, 1, 2
 RENDER_HDDA, RENDER_COUNT, RENDER_KEEP_MAJORANT, RENDER_RR = 1, 2, 4, 8
 RENDER_CACHE_NONE, RENDER_CACHE_LEAF, RENDER_COST_ORDER, RENDER_INDEX, RENDER_SPLIT = 16, 32, 64, 128, 256
-# accessor cache policy -> render flag (2 = last leaf and last lower node, the default)
+# accessor cache policy -> render flag (2: neither, the tree is read through the region index)
 CACHE_FLAGS = {0: RENDER_CACHE_NONE, 1: RENDER_CACHE_LEAF, 2: 0}
 # node layouts (bits): Morton child-slot order, SoA node words
 LAYOUT_V1, LAYOUT_MORTON, LAYOUT_SOA = 0, 1, 2
