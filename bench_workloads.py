@@ -359,8 +359,8 @@ def worstcase(args, torch, vdbc, synth, scenes, log):
 
 def iso(args, torch, vdbc, synth, scenes, log):
     """Iso-surface marcher at iso 0.5 (Section 5.4) on the 512^3 cloud at
-    1:10 and on the dense array: frame time and samples/s, with and without
-    empty-node skipping (VDB only), 1024x1024, step 0.5, 12 bisection steps."""
+    1:10 and on the dense array: frame time, with and without empty-node
+    skipping (VDB only), 1024x1024, step 0.5, 12 bisection steps."""
     n = args.size
     vol = synth.mid_volume(n=n)
     buf, st = vdbc.encode(vol, args.rate)
@@ -372,14 +372,15 @@ def iso(args, torch, vdbc, synth, scenes, log):
     rows = {}
     for name, field, flags, bg in (("vdb", g, 0, None), ("vdb_hdda", g, vdbc.RENDER_HDDA, None),
                                    ("dense", dense, 0, 0.0)):
-        # timed without the counter; evaluations from one more, counting launch
+        # timed without the counter; the evaluations of one more, counting launch,
+        # which visits samples that the timed launch skips: no rate follows from both
         r = vdbc.Renderer(field, cam, None, dict(base, flags=flags), vdbc.MODE_ISO, background=bg)
         rc = vdbc.Renderer(field, cam, None, dict(base, flags=flags | vdbc.RENDER_COUNT),
                            vdbc.MODE_ISO, background=bg)
         ms = _median_ms(torch, r.launch, 5)
         rc.launch()
         rows[name] = {"ms": round(ms, 3), "fps": round(1e3 / ms, 2),
-                      "samples_per_s": round(rc.sample_count() / ms * 1e3, 1),
+                      "samples_of_counting_launch": rc.sample_count(),
                       "hits": int((r.image[..., 3] == 1.0).sum().item())}
         log(f"[iso] {name}: {rows[name]}")
     best = min(("vdb", "vdb_hdda"), key=lambda k: rows[k]["ms"])
@@ -406,17 +407,15 @@ def ea(args, torch, vdbc, synth, scenes, log):
     rows = {}
     for name, field, flags, bg in (("vdb", g, 0, None), ("vdb_hdda", g, vdbc.RENDER_HDDA, None),
                                    ("dense", dense, 0, 0.0)):
-        # timed without the counter; samples of the lattice walk (which the
-        # timed launch may skip where they read nothing) from one more launch
+        # timed without the counter; the samples of one more, counting launch,
+        # which visits some that the timed launch skips: no rate follows from both
         r = vdbc.Renderer(field, cam, med, dict(base, flags=flags), vdbc.MODE_EA, background=bg)
         rc = vdbc.Renderer(field, cam, med, dict(base, flags=flags | vdbc.RENDER_COUNT),
                            vdbc.MODE_EA, background=bg)
         ms = _median_ms(torch, r.launch, 5)
         rc.launch()
-        taken = rc.sample_count()
-        rows[name] = {"ms": round(ms, 3), "fps": round(1e3 / ms, 2), "samples": taken,
-                      "samples_per_s": round(taken / ms * 1e3, 1),
-                      "gbs_at_32B_per_sample": round(taken * 32 / ms / 1e6, 1)}
+        rows[name] = {"ms": round(ms, 3), "fps": round(1e3 / ms, 2),
+                      "samples_of_counting_launch": rc.sample_count()}
         log(f"[ea] {name}: {rows[name]}")
     best = min(("vdb", "vdb_hdda"), key=lambda k: rows[k]["ms"])
     return {"metric": "emission-absorption frames/s, VDB (1:10) vs dense", "unit": "fps",
