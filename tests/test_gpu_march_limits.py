@@ -27,7 +27,7 @@ def _bits(t):
     return t.view(torch.int32).cpu().numpy()
 
 
-@pytest.mark.parametrize("voxels", [3.0e5, 1.0e6])
+@pytest.mark.parametrize("voxels", [8.0e3, 2.0e4, 3.2e4, 3.0e5, 1.0e6])
 def test_skipping_is_exact_from_far_away(voxels):
     # asked for or not, empty blocks change nothing: the image of every sample
     n = 256
@@ -78,3 +78,23 @@ def test_images_past_two_to_the_thirty_pixels():
             assert torch.equal(a.view(torch.int32), b.view(torch.int32)), y
         del r, every
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("distance", [0.8, 2.5])
+@pytest.mark.parametrize("flags", [0, vdbc.RENDER_HDDA])
+def test_long_volumes(distance, flags):
+    # a side of 20000: within and past what may be skipped by the region index
+    v = np.zeros((20000, 24, 31), np.float32)
+    rng = np.random.default_rng(8)
+    for z in (0, 3000, 9991, 19970):
+        v[z:z + 30] = rng.random((30, 24, 31), dtype=np.float32)
+    g = vdbc.Grid(vdbc.encode(v, 0.05)[0])
+    cam = scenes.orbit_camera(g.dims, 90, 60, azimuth_deg=3.0, elevation_deg=1.0, distance=distance,
+                              fov_y_deg=0.2)
+    for mode, med in ((vdbc.MODE_EA, scenes.ea_medium(8000.0)), (vdbc.MODE_ISO, None)):
+        prm = dict(step=0.5, iso=0.5, refine=5)
+        r = vdbc.Renderer(g, cam, med, dict(prm, flags=flags), mode)
+        every = vdbc.Renderer(g, cam, med, dict(prm, flags=flags | vdbc.RENDER_COUNT), mode)
+        got = _bits(r.launch())
+        assert np.array_equal(got, _bits(every.launch())), mode
+        assert len(np.unique(got)) > 20, mode
