@@ -725,7 +725,7 @@ __global__ __launch_bounds__(kThreads, NT == 4 && STAGED ? 4 : 1) void conv_dgra
 // zeros between them.
 // With LW the weights are staged behind the window: a wave has one to four
 // MFMAs per weight fragment, too few to cover a load from the L2 for each (64 ->
-// 32 channels, 8 x 256^2: 67 -> 63 us; its bytes at the copy rate take 32).
+// 32 channels, 8 x 256^2: 67 -> 57 us; its bytes at the copy rate take 32).
 template <int NT, bool LW>
 __global__ __launch_bounds__(kThreads) void conv_dgrad_s2_kernel(const uint16_t* __restrict__ dz, int coutp,
                                                                  int ho, int wo,

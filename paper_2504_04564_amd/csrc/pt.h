@@ -10,7 +10,7 @@ namespace vdbc {
 
 // Resident PT workgroups per compute unit (the kernel's launch bounds): the
 // tree accessor needs the registers of four, the others fit five (512^3 frame
-// 6.40 ms with four, 6.07 with five).
+// 5.52 ms with four, 5.22 with five; 994x676x1225 17.0 and 16.1).
 template <class Acc>
 constexpr int kPtBlocksPerCu = std::is_same_v<Acc, IndexAccT<false>> || std::is_same_v<Acc, IndexAccT<true>> ||
                                        std::is_same_v<Acc, DenseAcc> ? 5 : 4;
@@ -315,8 +315,8 @@ __device__ __forceinline__ long long to_fixed(float v) { return __float2ll_rn(v 
 // Bound by VALU issue (a wave instruction every four cycles of a SIMD, 90 % and
 // more of the time) with a third of the lanes active: what counts is the number
 // of instructions of a turn and the lanes that share them, not bytes.  512^3
-// frame (1024^2, 16 samples) 12.2 -> 5.45 ms in this kernel, 994x676x1225 full HD
-// with 64 samples 36 -> 15.8 ms, against a descent of the tree per lookup, Philox
+// frame (1024^2, 16 samples) 12.2 -> 5.4 ms in this kernel, 994x676x1225 full HD
+// with 64 samples 36 -> 15.5 ms, against a descent of the tree per lookup, Philox
 // at each draw and a way out of the turn at each event.
 // Delta-tracking path tracer (Section 4) over samples [s0, s1) of one tile of
 // 256 pixels.  The work item's 256 (s1 - s0) paths (unit u = sample u / 256
